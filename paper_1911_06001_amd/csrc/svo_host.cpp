@@ -719,6 +719,35 @@ int upload_frames(Scene& S, hipStream_t stream, bool to_device) {
     return SVO_OK;
 }
 
+// Copy a pool to the device in the device format (svo_internal.h), encoded
+// chunk by chunk on the way.
+hipError_t copy_pool(uint64_t* dev, const uint64_t* nodes, uint64_t n) {
+    constexpr uint64_t kChunk = 1u << 20;
+    const bool packed = n <= svo::kPackedNodes;
+    std::vector<uint64_t> buf(std::min(n, kChunk));
+    for (uint64_t at = 0; at < n; at += kChunk) {
+        const uint64_t cnt = std::min(kChunk, n - at);
+        for (uint64_t k = 0; k < cnt; ++k) {
+            const uint64_t w = nodes[at + k];
+            const uint32_t mask = nd_mask(w);
+            uint32_t w0 = 0u, w1 = nd_w1(w);   // a leaf: 0 and its colour
+            if (nd_xform(w)) {
+                w0 = svo::kNodeXform | mask;
+                w1 &= ~kXform;
+            } else if (mask) {
+                const bool far = nd_c24(w) == kFar;
+                const uint32_t child = far ? w1 : (uint32_t)(at + k) + nd_c24(w);
+                w0 = (packed ? child << 8 : (far ? svo::kNodeFarWide : 0u)) | mask;
+                w1 = child | ((packed && far) ? svo::kNodeFarPacked : 0u);
+            }
+            buf[k] = (uint64_t)w0 | ((uint64_t)w1 << 32);
+        }
+        const hipError_t e = hipMemcpy(dev + at, buf.data(), cnt * sizeof(uint64_t), hipMemcpyHostToDevice);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------ C ABI
@@ -877,12 +906,10 @@ int svo_upload(svo_ctx* ctx, const uint64_t* nodes, uint64_t n_nodes, uint32_t r
                 return fail(SVO_ENOMEM, "allocation of frame tables failed");
             }
         }
-        if (n_nodes) {
-            hipError_t e = hipMemcpy(S->d_nodes, nodes, n_nodes * sizeof(uint64_t), hipMemcpyHostToDevice);
-            if (e != hipSuccess) {
-                free_scene(*S);
-                return fail(SVO_EDEVICE, "pool copy failed: %s", hipGetErrorString(e));
-            }
+        const hipError_t e = copy_pool(S->d_nodes, nodes, n_nodes);
+        if (e != hipSuccess) {
+            free_scene(*S);
+            return fail(SVO_EDEVICE, "pool copy failed: %s", hipGetErrorString(e));
         }
         for (int k = 0; k < 2; ++k) (void)hipEventRecord(S->ev[k], 0);
         rc = upload_frames(*S, 0, true);
@@ -1063,8 +1090,7 @@ int launch(svo_ctx* ctx, const svo_config& cfg, svo::TraceArgs& a, hipStream_t s
     const uint64_t cap = (uint64_t)ctx->n_cu * resident_blocks(ctx, c, lds);
     L.blocks = (uint32_t)std::max<uint64_t>(1, std::min(want, cap));
     L.lds_bytes = lds;
-    const hipError_t e = a.counts ? svo::launch_trace_counted(a, L, st, inline_tab, inline_bytes)
-                                  : svo::launch_trace(a, L, st, inline_tab, inline_bytes);
+    const hipError_t e = svo::launch_trace(a, L, st, inline_tab, inline_bytes);
     if (e != hipSuccess) return fail(SVO_EDEVICE, "trace launch failed: %s", hipGetErrorString(e));
     return SVO_OK;
 }
@@ -1132,11 +1158,17 @@ struct PackedJob {
     svo::CameraArgs cam{};
 };
 
+// Whether a scene's node words carry only 32-bit child starts (see
+// kPackedNodes), and the bits of a node's word 1 that are its child start.
+bool wide_pool(const Scene& S) { return S.n_nodes > svo::kPackedNodes; }
+uint32_t child_mask(const Scene& S) { return wide_pool(S) ? ~0u : ~svo::kNodeFarPacked; }
+
 struct Packing {
     std::vector<PackedJob> jobs;        // non-empty jobs, in order
     uint64_t total = 0;
     uint32_t frames = 0, cands = 0, max_cand = 0, stack_levels = 1, nest_levels = 0, bvh = 0, bvh_depth = 0;
     const uint64_t* cache_src = nullptr;  // the pool with the most rays
+    bool wide = false;                  // some pool is wide
 };
 
 // Validate jobs (their scenes restricted to `allowed` when given), build the
@@ -1194,6 +1226,7 @@ int pack_jobs(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, const std::set
         P.max_cand = std::max(P.max_cand, Q.T.n_cand);
         P.stack_levels = std::max(P.stack_levels, Q.T.stack_levels);
         P.nest_levels = std::max(P.nest_levels, Q.T.nest_levels);
+        P.wide = P.wide || wide_pool(*S);
         rays_per_pool[S->d_nodes] += J.n;
         P.jobs.push_back(std::move(Q));
     }
@@ -1231,7 +1264,7 @@ void write_tables(const Packing& P, svo::JobRec* jr, svo::FrameRec* fr, uint32_t
         jr[i] = svo::JobRec{S.d_nodes, reinterpret_cast<const float4*>(J.rays), J.out_id, J.out_inst, J.out_t,
                             J.out_normal, begin, Q.frame_base, Q.cand_base, Q.T.n_cand,
                             S.d_nodes == P.cache_src ? cache_nodes : 0u, Q.bvh_base, Q.T.n_inline,
-                            Q.has_cam ? dev_cams + i : nullptr, 0};
+                            Q.has_cam ? dev_cams + i : nullptr, child_mask(S), 0};
         if (Q.has_cam) cams[i] = Q.cam;
         begin += J.n;
     }
@@ -1316,6 +1349,7 @@ int trace_rays(svo_ctx* ctx, svo_scene scene, const float* rays, uint64_t n, uin
     a.stack_levels = S->stack_levels;
     a.nest_levels = S->nest_levels;
     a.sort_cand = sorted ? 1u : 0u;
+    a.wide = wide_pool(*S) ? 1u : 0u;
     fill_common(cfg, a);
     a.reuse = reuse ? 1u : 0u;
     a.retraced = retraced;
@@ -1484,6 +1518,7 @@ int trace_batch(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, void* stream
         a.sort_cand = sorted ? 1u : 0u;
         a.stack_levels = P.stack_levels;
         a.nest_levels = P.nest_levels;
+        a.wide = P.wide ? 1u : 0u;
         fill_common(cfg, a);
         if (P.jobs.size() == 1 && P.jobs[0].has_cam) {
             // one job: its camera travels in the arguments
@@ -1619,6 +1654,7 @@ int svo_plan_create(svo_ctx* ctx, const svo_scene* scenes, uint32_t n_scenes, co
             pl->scenes.insert(scenes[i]);
             pl->stack_cap = std::max(pl->stack_cap, stack_bound(*S));
             pl->nest_cap = std::max(pl->nest_cap, std::min<uint32_t>(svo::kMaxInlineNest, S->an.max_nesting));
+            if (wide_pool(*S)) pl->args.wide = 1u;
             max_slots = std::max(max_slots, S->n_slots);
             max_pool = std::max(max_pool, S->n_nodes);
         }
@@ -1641,7 +1677,9 @@ int svo_plan_create(svo_ctx* ctx, const svo_scene* scenes, uint32_t n_scenes, co
         pl->bytes = pl->off_cams + (size_t)pl->max_jobs * sizeof(svo::CameraArgs);
 
         svo::TraceArgs& a = pl->args;
+        const uint32_t wide = a.wide;
         a = svo::TraceArgs{};
+        a.wide = wide;
         a.n_jobs = pl->max_jobs;
         a.n_frames = pl->max_frames;
         a.n_cand_total = pl->max_frames;

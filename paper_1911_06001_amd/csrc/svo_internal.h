@@ -30,6 +30,23 @@ enum : uint32_t {
     FR_INLINE = 1u << 15,     // moved content stays in its static cell: entered in place
 };
 
+// A pool node as the device reads it (made from the upload format when a
+// scene is uploaded): word 0 and word 1, 32 bits each.
+//   leaf         0; its colour
+//   interior     child mask in the low byte, and above it, in a pool of at
+//                most kPackedNodes nodes, the absolute child start; word 1 is
+//                the child start in any pool
+//   transformed  kNodeXform | child mask; its slot
+// So the walk tells the three apart by word 0 alone, needs no far-pointer
+// case, and in pools of up to kPackedNodes nodes word 0 is all that it keeps
+// of a node.  An interior node whose child start came through a far pointer
+// is marked (kNodeFarPacked in word 1 of a packed pool, kNodeFarWide in word
+// 0 of a wider one): svo_shade reads word 1 of any id it is given.
+constexpr uint32_t kNodeXform = 0xFFFFFF00u;
+constexpr uint64_t kPackedNodes = 0xFFFFFFu;   // child starts stay below kNodeXform >> 8
+constexpr uint32_t kNodeFarPacked = 0x80000000u;
+constexpr uint32_t kNodeFarWide = 0x100u;
+
 // Frames entered in place may nest this deep inside one top-level frame.
 constexpr uint32_t kMaxInlineNest = 4;
 // Per-lane candidate entry tables are kept in LDS up to this many candidates;
@@ -83,7 +100,8 @@ struct alignas(16) JobRec {
     uint32_t bvh_base;        // the job's hierarchy root in the launch's node array
     uint32_t n_inline;        // in-place frames, listed after the job's candidates
     const CameraArgs* cam;    // device camera making the job's rays (rays unused), or nullptr
-    uint64_t pad;
+    uint32_t child_mask;      // bits of a node's word 1 that are its child start
+    uint32_t pad;
 };
 static_assert(sizeof(JobRec) == 96, "job record must be 96 bytes");
 
@@ -233,6 +251,7 @@ struct TraceArgs {
     uint32_t lds_nodes;       // pool prefix cached in LDS (even)
     uint32_t stack_levels;    // traversal stack entries per lane
     uint32_t nest_levels;     // frame stack entries per lane (inline frames)
+    uint32_t wide;            // 1: some pool has more than kPackedNodes nodes
     uint32_t sort_cand;       // 1: candidates in entry order via a per-lane LDS table
     uint32_t refill;          // a wave claims new rays once this many lanes are idle (1..64)
     uint32_t claim;           // rays a wave takes from a partition counter at once (a multiple of 64)
@@ -295,7 +314,7 @@ hipError_t launch_ao_rays(const AoArgs& a, hipStream_t stream);
 
 // Compositing into an RGBA8 image (see svo_raygen.hip).
 struct ShadeArgs {
-    const uint64_t* nodes;    // the scene's pool: a leaf's word1 is its RGBA8 colour
+    const uint64_t* nodes;    // the scene's pool (device format): a leaf's word 1 is its RGBA8 colour
     uint64_t n_nodes;         // ids at or beyond this count as misses
     const uint32_t* prim_id;  // width * height * samples, ray order
     const uint32_t* ao_id;    // k per primary ray (nullable when k == 0)
@@ -320,11 +339,9 @@ size_t trace_lds_bytes(const TraceArgs& a, uint32_t waves_per_block);
 // captured into a graph) changes the kernel's attributes.
 hipError_t prepare_trace(size_t max_lds);
 // inline_tab (nullable): the frame table to pass in the arguments (at most
-// kInlineTableBytes; one-job launches with sorted candidates only).
+// kInlineTableBytes; one-job launches with sorted candidates only).  With
+// a.counts the counting instantiation (single-job launches only).
 hipError_t launch_trace(const TraceArgs& a, const LaunchCfg& c, hipStream_t stream,
                         const unsigned char* inline_tab = nullptr, size_t inline_bytes = 0);
-// The counting instantiation (a.counts set; single-job launches only).
-hipError_t launch_trace_counted(const TraceArgs& a, const LaunchCfg& c, hipStream_t stream,
-                                const unsigned char* inline_tab = nullptr, size_t inline_bytes = 0);
 
 }  // namespace svo

@@ -67,6 +67,15 @@ __global__ __launch_bounds__(256) void ao_rays_kernel(AoArgs a) {
     }
 }
 
+// Word 1 of a node in the upload format (a leaf's colour) from its device
+// words.
+__device__ __forceinline__ uint32_t upload_word1(uint64_t w, bool packed) {
+    const uint32_t w0 = (uint32_t)w, w1 = (uint32_t)(w >> 32);
+    if (w0 == 0u) return w1;
+    if (w0 >= kNodeXform) return w1 | 0x80000000u;
+    return (packed ? (w1 & kNodeFarPacked) : (w0 & kNodeFarWide)) ? (packed ? w1 & ~kNodeFarPacked : w1) : 0u;
+}
+
 // Composite one pixel per thread, in integers: sample i of the pixel has
 // leaf colour c (RGB of the hit leaf's word1; the background for a miss,
 // which is any id outside the pool)
@@ -84,7 +93,7 @@ __global__ __launch_bounds__(256) void shade_kernel(ShadeArgs a) {
             uint32_t col = a.background;
             uint64_t w = den;
             if ((uint64_t)id < a.n_nodes) {
-                col = (uint32_t)(a.nodes[id] >> 32);
+                col = upload_word1(a.nodes[id], a.n_nodes <= kPackedNodes);
                 uint32_t occ = 0;
                 for (uint32_t j = 0; j < a.k; ++j) occ += (a.ao_id[i * a.k + j] != 0xFFFFFFFFu) ? 1u : 0u;
                 w = (uint64_t)a.ambient * a.k + (uint64_t)(1000u - a.ambient) * (a.k - occ);

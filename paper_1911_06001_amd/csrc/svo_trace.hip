@@ -10,8 +10,9 @@
 //   3. walk the frame's octree front to back, top-down (the role of the
 //      parametric traversal in the paper, Sec. 5): integer cell corners, a
 //      per-level LDS stack of (child start, mask), and an exit by the highest
-//      changed coordinate bit, so popping needs no search (5 bytes per
-//      level and lane: a 32-bit child start and an 8-bit mask);
+//      changed coordinate bit, so popping needs no search (4 bytes per
+//      level and lane: a 24-bit child start and an 8-bit mask in one word;
+//      5 bytes where a pool needs wider child starts, see kWide);
 //   4. at a transformed node whose moved content stays inside its static
 //      cell, switch into that node's frame in place (Sec. 3, Fig. 1: the ray,
 //      not the model, is transformed) and resume the enclosing walk after it;
@@ -57,8 +58,6 @@ namespace {
 
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 constexpr uint32_t kStepLimitId = 0xFFFFFFFEu;
-constexpr uint32_t kXform = 0x80000000u;
-
 enum : uint32_t { M_DONE = 0, M_WALK = 1, M_SELECT = 2 };
 enum : uint32_t { EV_NONE = 0, EV_HIT = 1, EV_ENTER = 2, EV_END = 3, EV_LIMIT = 4 };
 enum : uint32_t { PEND_RESUME = 1, PEND_ROOT_HIT = 2 };
@@ -294,6 +293,11 @@ template <typename T>
 __device__ __forceinline__ T gld(const T* p, uint64_t i) {
     return ((const __attribute__((address_space(1))) T*)p)[i];
 }
+// The 8-byte word at a 32-bit byte offset from a wave-uniform base (the
+// scalar-base form of the load: no 64-bit address arithmetic per lane).
+__device__ __forceinline__ uint64_t gld_at32(const uint64_t* p, uint32_t byte) {
+    return *(const __attribute__((address_space(1))) uint64_t*)((const __attribute__((address_space(1))) char*)p + byte);
+}
 template <typename T>
 __device__ __forceinline__ void gst(T* p, uint64_t i, T v) {
     ((__attribute__((address_space(1))) T*)p)[i] = v;
@@ -307,12 +311,19 @@ __host__ __device__ __forceinline__ size_t cand_lane_bytes(const TraceArgs& a) {
     return a.sort_cand ? (size_t)a.max_cand * 4 : (a.max_cand ? (size_t)(a.bvh_depth + 1) * 4 : 0);
 }
 
+// Traversal-stack slots per lane: slot sb + h holds the node whose children
+// are the cells of size 2^h of the frame at base sb; the frame root's own
+// level needs none.
+__host__ __device__ __forceinline__ uint32_t stack_slots(const TraceArgs& a) { return a.stack_levels - 1u; }
+__host__ __device__ __forceinline__ uint32_t stack_slot_bytes(const TraceArgs& a) { return a.wide ? 5u : 4u; }
+
 size_t trace_lds_bytes(const TraceArgs& a, uint32_t waves_per_block) {
     const size_t shared = align16((size_t)a.lds_nodes * 8) + (size_t)a.n_frames * 80 +
                           align16((size_t)a.n_cand_total * 4) + (size_t)a.n_jobs * sizeof(JobRec) +
                           (size_t)a.n_bvh_total * sizeof(BvhNode) + (a.jobs ? 0 : kHotLdsBytes) +
                           (a.has_cam0 ? sizeof(CameraArgs) : 0);
-    const size_t per_wave = cand_lane_bytes(a) * 64 + (size_t)a.stack_levels * 64 * 5 + (size_t)a.nest_levels * 64 * 16;
+    const size_t per_wave = cand_lane_bytes(a) * 64 + align16((size_t)stack_slots(a) * 64 * stack_slot_bytes(a)) +
+                            (size_t)a.nest_levels * 64 * 16;
     return shared + per_wave * waves_per_block;
 }
 
@@ -323,15 +334,19 @@ size_t trace_lds_bytes(const TraceArgs& a, uint32_t waves_per_block) {
 // for 6 resident waves per SIMD (80 VGPRs): the few values that then go to
 // scratch are per-ray state outside the walk loop, and the extra waves hide
 // more of the node-load latency.  The hierarchy one keeps its natural
-// count (102 VGPRs single-job, 110 batched): forcing it lower spills inside
-// its candidate search.
+// count (97 VGPRs single-job, 108 batched; 103 and 112 wide): forcing it
+// lower spills inside its candidate search.
 // kSingle: a one-job launch (the job in the arguments), whose pool, cache
 // size and table offsets are then launch-wide values (scalar registers)
 // rather than per-lane ones.
 // kInline: the frame table comes in the arguments (TraceArgsInline).
+// kWide: some pool of the launch has more than kPackedNodes nodes.  Its child
+// starts do not fit the 24 bits beside a mask, so the stack keeps a 32-bit
+// start and a mask byte apart (two LDS accesses and two addresses where the
+// packed word takes one); smaller pools take the packed instantiations.
 // kCount: the counting build (TraceArgs::counts and trail), for tests and
 // measurement only.
-template <bool kSorted, bool kSingle, bool kInline = false, bool kCount = false>
+template <bool kSorted, bool kSingle, bool kInline, bool kWide, bool kCount = false>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 6 : 1, 8))) void trace_kernel(
     typename std::conditional<kInline, TraceArgsInline, TraceArgs>::type a) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -359,17 +374,19 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = threadIdx.x >> 6;
     const size_t ent_bytes = cand_lane_bytes(a) * 64;
-    const size_t per_wave = ent_bytes + (size_t)a.stack_levels * 64 * 5 + (size_t)a.nest_levels * 64 * 16;
+    const size_t stack_bytes = (size_t)stack_slots(a) * 64 * (kWide ? 5 : 4);
+    const size_t per_wave = ent_bytes + stack_bytes + (size_t)a.nest_levels * 64 * 16;
     const uint32_t bst_cap = a.bvh_depth + 1;
     unsigned char* wp = p + per_wave * wave;
     float* ent = reinterpret_cast<float*>(wp) + lane;                                   // candidate c at ent[c * 64]
     // hierarchy stack entry k at bst[k * 64]: a box index; its entry is tested
     // again when popped, against the best hit by then
     uint32_t* bst = reinterpret_cast<uint32_t*>(wp) + lane;
-    // traversal stack, slot l: child start at stkc[l * 64], child mask at stkm[l * 64]
+    // traversal stack, slot l: the node word at stkc[l * 64]; kWide: the
+    // child start there and the child mask at stkm[l * 64]
     uint32_t* stkc = reinterpret_cast<uint32_t*>(wp + ent_bytes) + lane;
-    uint8_t* stkm = reinterpret_cast<uint8_t*>(wp + ent_bytes + (size_t)a.stack_levels * 256) + lane;
-    uint4* fst = reinterpret_cast<uint4*>(wp + ent_bytes + (size_t)a.stack_levels * 320) + lane;  // nest n at fst[n * 64]
+    uint8_t* stkm = reinterpret_cast<uint8_t*>(wp + ent_bytes + (size_t)stack_slots(a) * 256) + lane;
+    uint4* fst = reinterpret_cast<uint4*>(wp + ent_bytes + stack_bytes) + lane;  // nest n at fst[n * 64]
 
     // launch-wide counts: the arguments, or a plan's header (capacities
     // above bound them, so every LDS copy below stays in its region)
@@ -511,15 +528,19 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     // leaf's end, 22-31 stack depth
     uint32_t bws = 0;
     FrameRay fr{};
-    uint32_t cur_f = 0, pmask = 0, pchild = 0, px = 0, py = 0, pz = 0, size = 1, nest = 0;
-    // stack slots: the current frame's levels start at sbase; slot = sbase +
-    // level of the current cell, top = sbase + K (so size = 2^(top - slot)).
-    // Slot s holds the child start and mask of the node on the current path
-    // whose children are the cells of level s - sbase: pchild and pmask are
-    // always a copy of the current slot, so leaving cells up to any level is
-    // a plain read.
-    uint32_t slot = 1, sbase = 0, top = 0;
+    // the current cell: corner (px, py, pz), size 2^h, reached at tc0; pw is
+    // the word of its parent node (mask in the low byte, child start above;
+    // kWide: the child start in pchild, the bits above the mask undefined)
+    uint32_t cur_f = 0, pw = 0, pchild = 0, px = 0, py = 0, pz = 0, h = 0, nest = 0;
+    // the current frame's stack slots start at fs (slot 0 of the frame: cells
+    // of size 1).  The slot of size 2^h holds the node on the current path
+    // whose children have that size: pw (and pchild) always copy the current
+    // slot, so leaving cells up to any level is a plain read.  A frame
+    // entered in place takes the slots below its cell's.
+    uint32_t* fs = stkc;
+    [[maybe_unused]] uint8_t* fsm = stkm;
     uint32_t lds_last = n_lds ? n_lds - 1u : 0u;  // the last cached node index (0 with no cache: reads stay in bounds)
+    [[maybe_unused]] uint32_t cmask = ~0u;        // child start bits of a job's node words (kWide, several jobs)
     float tc0 = 0.f;
     // what the next walk step does first: PEND_RESUME continue just past a
     // transformed cell the walk came back from; PEND_ROOT_HIT the frame root
@@ -542,6 +563,42 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
         }
     };
 
+    // The children of node word w0 (child start c) become the cells walked,
+    // of size 2^h: into the registers and their stack slot.
+    auto set_node = [&](uint32_t w0, uint32_t c) {
+        pw = w0;
+        if constexpr (kWide) {
+            pchild = c;
+            fs[h * 64] = c;
+            fsm[h * 64] = (uint8_t)w0;
+        } else {
+            fs[h * 64] = w0;
+        }
+    };
+    // ... and back from their stack slot.
+    auto load_node = [&]() {
+        if constexpr (kWide) {
+            pchild = fs[h * 64];
+            pw = fsm[h * 64];
+        } else {
+            pw = fs[h * 64];
+        }
+    };
+    // Stack slots from sb on; a frame record's root as a node word.
+    auto set_slots = [&](uint32_t sb) {
+        fs = stkc + sb * 64;
+        if constexpr (kWide) fsm = stkm + sb * 64;
+    };
+    auto root_word = [&](const FrameRec& F) -> uint32_t { return kWide ? F.info : (F.child << 8) | (F.info & FR_MASK); };
+    // First cell of a frame entered at t: the root's child that holds it.
+    auto first_cell = [&](float t) {
+        const float half = (float)(1u << h);
+        px = (fmaf(half, fr.ix, fr.bx) <= t) ? (1u << h) : 0u;
+        py = (fmaf(half, fr.iy, fr.by) <= t) ? (1u << h) : 0u;
+        pz = (fmaf(half, fr.iz, fr.bz) <= t) ? (1u << h) : 0u;
+        tc0 = t;
+    };
+
     // Enter top-level frame f from its root.  Returns true when a walk starts.
     auto start_frame = [&](uint32_t f) -> bool {
         const FrameRec& F = lds_frames[f];
@@ -555,23 +612,15 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
         cur_f = f;
         if (F.info & FR_ROOT_LEAF) {
             px = py = pz = 0u;
-            size = 1u << fr.K;
+            h = fr.K;
             pend = PEND_ROOT_HIT;
             return true;
         }
-        pmask = F.info & FR_MASK;
-        pchild = F.child;
-        sbase = 0;
-        slot = 1;
-        top = fr.K;
-        stkc[slot * 64] = pchild;
-        stkm[slot * 64] = (uint8_t)pmask;
+        h = fr.K - 1u;
+        set_slots(stack_slots(a) - fr.K);
+        set_node(root_word(F), F.child);
         nest = 0;
-        size = 1u << (fr.K - 1);
-        px = (fmaf((float)size, fr.ix, fr.bx) <= t0) ? size : 0u;
-        py = (fmaf((float)size, fr.iy, fr.by) <= t0) ? size : 0u;
-        pz = (fmaf((float)size, fr.iz, fr.bz) <= t0) ? size : 0u;
-        tc0 = t0;
+        first_cell(t0);
         pend = 0;
         return true;
     };
@@ -798,6 +847,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
                         nodes = J.nodes;
                         n_lds = min(J.lds_nodes, fill_nodes);
                         lds_last = n_lds ? n_lds - 1u : 0u;
+                        if constexpr (kWide) cmask = J.child_mask;
                         fbase = J.frame_base;
                         cbase = J.cand_base;
                         ncand = J.n_cand;
@@ -896,74 +946,85 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
 
         // ---------------------------------------------------------- walk
         if (mode == M_WALK) {
-            // Leave the current cell through its nearest exit plane(s); EV_END
-            // when the ray leaves the frame's root cell or passes tl.
-            auto advance = [&](float ex, float ey, float ez, float tc1) -> uint32_t {
-                const bool sx = ex == tc1, sy = ey == tc1, sz = ez == tc1;
-                const uint32_t nx = px + (sx ? size : 0u);
-                const uint32_t ny = py + (sy ? size : 0u);
-                const uint32_t nz = pz + (sz ? size : 0u);
-                // the new cell's size is 2^h, h the highest changed corner bit;
-                // no plane at tc1 (a NaN) leaves diff = 0 and h = 2^32 - 1
-                const uint32_t diff = (nx ^ px) | (ny ^ py) | (nz ^ pz);
-                const uint32_t h = 31u - __clz(diff);
-                // descents between two advances are bounded by the depth, so
-                // counting advances bounds the walk
-                ++steps;
-                const uint32_t ev = (tc1 > tl || h >= fr.K) ? EV_END : (steps > a.step_limit ? EV_LIMIT : EV_NONE);
-                if (ev != EV_NONE) return ev;
-                const uint32_t nsize = 1u << h;
-                const uint32_t keep = ~(nsize - 1u);
-                px = nx & keep;
-                py = ny & keep;
-                pz = nz & keep;
-                slot = top - h;  // at or above the current level
-                pchild = stkc[slot * 64];
-                pmask = stkm[slot * 64];
-                size = nsize;
-                tc0 = tc1;
-                return EV_NONE;
+            // The octant of the current cell in its parent (bit h of each
+            // corner, unmirrored), and whether the parent has that child.
+            uint32_t oct = 0;
+            auto occupied = [&]() -> bool {
+                oct = (__builtin_amdgcn_ubfe(px, h, 1) | (__builtin_amdgcn_ubfe(py, h, 1) << 1) |
+                       (__builtin_amdgcn_ubfe(pz, h, 1) << 2)) ^ fr.flip;
+                return __builtin_amdgcn_ubfe(pw, oct, 1) != 0u;
             };
             uint32_t ev = EV_NONE;
-            uint32_t hit_id = 0, xf = 0;
-            float xf_tc1 = 0.f;
+            uint32_t evd = 0;   // the leaf hit, or the frame to enter
             const bool hit_root = pend == PEND_ROOT_HIT;
+            // PEND_RESUME: continue just past a transformed cell the walk
+            // came back from, as past an empty one
+            bool full = pend == 0u && occupied();
+            pend = 0;
+            bool go = !hit_root;
             if (hit_root) {
-                pend = 0;
                 ev = EV_HIT;
-                hit_id = lds_frames[cur_f].root;
-            } else if (pend == PEND_RESUME) {
-                // continue just past a transformed cell the walk came back from
-                pend = 0;
-                const float ex = fmaf((float)(px + size), fr.ix, fr.bx);
-                const float ey = fmaf((float)(py + size), fr.iy, fr.by);
-                const float ez = fmaf((float)(pz + size), fr.iz, fr.bz);
-                ev = advance(ex, ey, ez, min3f(ex, ey, ez));
+                evd = lds_frames[cur_f].root;
             }
-            // the hot loop: visit, descend or advance until something happens
-            while (ev == EV_NONE) {
-                const float ex = fmaf((float)(px + size), fr.ix, fr.bx);
-                const float ey = fmaf((float)(py + size), fr.iy, fr.by);
-                const float ez = fmaf((float)(pz + size), fr.iz, fr.bz);
-                const float tc1 = min3f(ex, ey, ez);
-                // the cell's octant in its parent: bit h of each corner (size = 2^h)
-                const uint32_t h = top - slot;
-                const uint32_t oct = (__builtin_amdgcn_ubfe(px, h, 1) | (__builtin_amdgcn_ubfe(py, h, 1) << 1) |
-                                      (__builtin_amdgcn_ubfe(pz, h, 1) << 2)) ^ fr.flip;
-                if (__builtin_amdgcn_ubfe(pmask, oct, 1)) {
-                    const uint32_t cidx = pchild + __popc(pmask & ((1u << oct) - 1u));
-                    // the child's corner does not depend on the node: computed
-                    // while its load is in flight
-                    const uint32_t hs = size >> 1;
-                    const uint32_t cx = px + ((fmaf((float)(px + hs), fr.ix, fr.bx) <= tc0) ? hs : 0u);
-                    const uint32_t cy = py + ((fmaf((float)(py + hs), fr.iy, fr.by) <= tc0) ? hs : 0u);
-                    const uint32_t cz = pz + ((fmaf((float)(pz + hs), fr.iz, fr.bz) <= tc0) ? hs : 0u);
-                    // separate LDS and global reads (a select between the two
-                    // would become one generic load waiting on both counters)
-                    const uint64_t wl = lds_nodes[min(cidx, lds_last)];
-                    uint64_t wg = 0;
-                    if (cidx >= n_lds) wg = gld(nodes, cidx);
-                    const uint64_t w = (cidx < n_lds) ? wl : wg;
+            // The hot loop, until something happens.  Bound by VALU issue
+            // while tiles are left and by the chain of one lane's turns at the
+            // end.  Each turn leaves the current cell if it is empty, then
+            // descends into the cell it now stands in if that one is not: some
+            // lane of a wave needs either half on most turns, so a lane that
+            // needs one after the other gets both from one turn.  Per 64-ray
+            // tile of the 1080p terrain that is 14.4 turns running the halves
+            // 12.1 and 12.9 times; a loop of one step (advance or descend) per
+            // turn took 19.5 turns and 15.0 and 15.8 halves, and a second
+            // advance per turn runs more instructions than it saves.  A turn
+            // is about 77 VALU instructions (about 115 with child offsets
+            // relative to the node, the child start and mask apart in the
+            // stack and the exit planes computed for both halves).  Measured
+            // against that loop: 1080p terrain animation 176 -> 145 us,
+            // 4096^3 terrain at 4K 2,186 -> 1,846 us, 1080p instances 401 ->
+            // 334 us, 256x256 sphere 64 -> 54 us.
+            while (go) {
+                if (!full) {
+                    // advance: leave the cell through its nearest exit
+                    // plane(s); the new cell's size is 2^h2, h2 the highest
+                    // changed corner bit (no plane at tc1, a NaN, changes
+                    // none and ends the walk).  Descents between two advances
+                    // are bounded by the depth, so counting advances bounds
+                    // the walk.
+                    const uint32_t size = 1u << h;
+                    const uint32_t qx = px + size, qy = py + size, qz = pz + size;
+                    const float ex = fmaf((float)qx, fr.ix, fr.bx);
+                    const float ey = fmaf((float)qy, fr.iy, fr.by);
+                    const float ez = fmaf((float)qz, fr.iz, fr.bz);
+                    const float tc1 = min3f(ex, ey, ez);
+                    const uint32_t nx = (ex == tc1) ? qx : px;
+                    const uint32_t ny = (ey == tc1) ? qy : py;
+                    const uint32_t nz = (ez == tc1) ? qz : pz;
+                    const uint32_t diff = (nx ^ px) | (ny ^ py) | (nz ^ pz);
+                    const uint32_t h2 = 31u - (diff ? (uint32_t)__builtin_clz(diff) : ~0u);
+                    ++steps;
+                    const bool on = tc1 <= tl && h2 < fr.K;
+                    if (on && steps <= a.step_limit) {
+                        const uint32_t keep = ~0u << h2;
+                        px = nx & keep;
+                        py = ny & keep;
+                        pz = nz & keep;
+                        h = h2;
+                        tc0 = tc1;
+                        load_node();
+                        full = occupied();
+                    } else {
+                        ev = on ? EV_LIMIT : EV_END;
+                        go = false;
+                    }
+                }
+                if (full) {
+                    // descend: the child's node word, from the LDS copy of the
+                    // pool's prefix or from the pool (separate LDS and global
+                    // reads: a select between the two would become one generic
+                    // load waiting on both counters)
+                    const uint32_t cidx = (kWide ? pchild : pw >> 8) + __popc(__builtin_amdgcn_ubfe(pw, 0, oct));
+                    uint64_t w = lds_nodes[min(cidx, lds_last)];
+                    if (cidx >= n_lds) w = kWide ? gld(nodes, cidx) : gld_at32(nodes, cidx * 8u);
                     if constexpr (kCount) {
                         if (a.trail && c_trail < a.trail_cap)
                             gst(a.trail, (uint64_t)c_trail * n_rays + gray, cidx | ((cidx < n_lds) ? 0x80000000u : 0u));
@@ -972,35 +1033,30 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
                     }
                     const uint32_t w0 = (uint32_t)w;
                     const uint32_t w1 = (uint32_t)(w >> 32);
-                    const uint32_t cm = w0 & 0xFFu;
-                    if (cm == 0u) {
+                    if (w0 - 1u < kNodeXform - 1u) {
+                        // an interior node: into the child that holds the
+                        // ray's point at tc0
+                        h -= 1u;
+                        const uint32_t hs = 1u << h;
+                        const uint32_t cx = px | hs, cy = py | hs, cz = pz | hs;
+                        px = (fmaf((float)cx, fr.ix, fr.bx) <= tc0) ? cx : px;
+                        py = (fmaf((float)cy, fr.iy, fr.by) <= tc0) ? cy : py;
+                        pz = (fmaf((float)cz, fr.iz, fr.bz) <= tc0) ? cz : pz;
+                        set_node(w0, (kSingle || !kWide) ? w1 : (w1 & cmask));
+                        full = occupied();
+                    } else if (w0 == 0u) {
                         ev = EV_HIT;
-                        hit_id = cidx;
-                        break;
+                        evd = cidx;
+                        go = false;
+                    } else {
+                        evd = fbase + 1u + w1;
+                        full = false;   // a candidate frame: traced on its own, empty here
+                        if (lds_frames[evd].info & FR_INLINE) {
+                            ev = EV_ENTER;
+                            go = false;
+                        }
                     }
-                    if (!(w1 & kXform)) {
-                        const uint32_t c24 = w0 >> 8;
-                        pchild = (c24 == 0xFFFFFFu) ? w1 : cidx + c24;
-                        pmask = cm;
-                        ++slot;
-                        stkc[slot * 64] = pchild;
-                        stkm[slot * 64] = (uint8_t)pmask;
-                        size = hs;
-                        px = cx;
-                        py = cy;
-                        pz = cz;
-                        continue;
-                    }
-                    const uint32_t f = fbase + 1u + (w1 & 0x7FFFFFFFu);
-                    if (lds_frames[f].info & FR_INLINE) {
-                        ev = EV_ENTER;
-                        xf = f;
-                        xf_tc1 = tc1;
-                        break;
-                    }
-                    // a candidate frame: traced on its own, empty here
                 }
-                ev = advance(ex, ey, ez, tc1);
             }
             if (ev == EV_HIT) {
                 // the first solid leaf front to back ends this top-level frame;
@@ -1008,8 +1064,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
                 // walk goes on past it; a frame root leaf ends the frame)
                 int ha;
                 float th;
-                if (exact_hit(xmaps + (size_t)kExactMapDoubles * cur_f, r, fr, px, py, pz, size, th, ha)) {
-                    record_hit(th, hit_id, cur_f, ha);
+                if (exact_hit(xmaps + (size_t)kExactMapDoubles * cur_f, r, fr, px, py, pz, 1u << h, th, ha)) {
+                    record_hit(th, evd, cur_f, ha);
                     mode = M_SELECT;
                     nest = 0;
                 } else if (hit_root) {
@@ -1022,33 +1078,28 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
                 best_id = kStepLimitId;
                 finish();
             } else if (ev == EV_ENTER) {
-                const FrameRec& C = lds_frames[xf];
+                const FrameRec& C = lds_frames[evd];
                 FrameRay cfr;
                 float t0;
-                if (frame_setup<true>(C, r, fminf(tl, xf_tc1), cfr, t0)) {
+                // no later than the ray's way out of the cell
+                const float cell_out = min3f(fmaf((float)(px + (1u << h)), fr.ix, fr.bx), fmaf((float)(py + (1u << h)), fr.iy, fr.by),
+                                             fmaf((float)(pz + (1u << h)), fr.iz, fr.bz));
+                if (frame_setup<true>(C, r, fminf(tl, cell_out), cfr, t0)) {
                     if constexpr (kCount) {
                         ++c_frames;
                         ++c_nodes;   // the frame's root record
                     }
                     // save where the enclosing walk stands (its current slot
                     // keeps its node), then enter in place
-                    fst[nest * 64] =
-                        make_uint4(cur_f | ((slot - sbase) << 11) | (sbase << 16), px, py, pz);
+                    const uint32_t sb = (uint32_t)(fs - stkc) >> 6;
+                    fst[nest * 64] = make_uint4(cur_f | (h << 11) | (sb << 16), px, py, pz);
                     ++nest;
-                    sbase = slot;
-                    cur_f = xf;
+                    cur_f = evd;
                     fr = cfr;
-                    pmask = C.info & FR_MASK;
-                    pchild = C.child;
-                    slot = sbase + 1u;
-                    top = sbase + fr.K;
-                    stkc[slot * 64] = pchild;
-                    stkm[slot * 64] = (uint8_t)pmask;
-                    size = 1u << (fr.K - 1);
-                    px = (fmaf((float)size, fr.ix, fr.bx) <= t0) ? size : 0u;
-                    py = (fmaf((float)size, fr.iy, fr.by) <= t0) ? size : 0u;
-                    pz = (fmaf((float)size, fr.iz, fr.bz) <= t0) ? size : 0u;
-                    tc0 = t0;
+                    set_slots(sb + h - fr.K);
+                    h = fr.K - 1u;
+                    set_node(root_word(C), C.child);
+                    first_cell(t0);
                 } else {
                     pend = PEND_RESUME;  // missed it: the cell is empty for this ray
                 }
@@ -1058,18 +1109,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
                     --nest;
                     const uint4 e = fst[nest * 64];
                     cur_f = e.x & 0x7FFu;
-                    const uint32_t lvl = (e.x >> 11) & 31u;
-                    sbase = (e.x >> 16) & 127u;
-                    slot = sbase + lvl;
+                    h = (e.x >> 11) & 31u;
+                    set_slots((e.x >> 16) & 127u);
                     px = e.y;
                     py = e.z;
                     pz = e.w;
                     float t0;
                     frame_setup<true>(lds_frames[cur_f], r, tl, fr, t0);
-                    size = 1u << (fr.K - lvl);
-                    top = sbase + fr.K;
-                    pchild = stkc[slot * 64];
-                    pmask = stkm[slot * 64];
+                    load_node();
                     pend = PEND_RESUME;
                 } else {
                     mode = M_SELECT;
@@ -1081,11 +1128,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
             // the next walk step); saying so frees its registers for the
             // candidate search
             fr = FrameRay{};
-            px = py = pz = 0;
-            size = 1;
-            pchild = pmask = 0;
-            slot = 1;
-            sbase = top = 0;
+            px = py = pz = h = 0;
+            pw = pchild = 0;
+            fs = stkc;
+            fsm = stkm;
             cur_f = nest = 0;
             tc0 = 0.f;
             pend = 0;
@@ -1278,17 +1324,35 @@ hipError_t launch_zero_words(uint32_t* p, uint32_t n, hipStream_t stream) {
     return hipGetLastError();
 }
 
+namespace {
+
+// The instantiation of a launch, to be launched or to have its attributes
+// set (f takes the kernel and whether it takes a TraceArgsInline).
+template <bool kWide, typename F>
+hipError_t with_kernel(bool sorted, bool single, bool inline_tab, bool count, F&& f) {
+    if (count) {
+        if (inline_tab) return f(&trace_kernel<true, true, true, kWide, true>);
+        return sorted ? f(&trace_kernel<true, true, false, kWide, true>) : f(&trace_kernel<false, true, false, kWide, true>);
+    }
+    if (inline_tab) return f(&trace_kernel<true, true, true, kWide>);
+    if (sorted) return single ? f(&trace_kernel<true, true, false, kWide>) : f(&trace_kernel<true, false, false, kWide>);
+    return single ? f(&trace_kernel<false, true, false, kWide>) : f(&trace_kernel<false, false, false, kWide>);
+}
+
+template <typename F>
+hipError_t with_kernel(bool wide, bool sorted, bool single, bool inline_tab, bool count, F&& f) {
+    return wide ? with_kernel<true>(sorted, single, inline_tab, count, f)
+                : with_kernel<false>(sorted, single, inline_tab, count, f);
+}
+
+}  // namespace
+
 hipError_t prepare_trace(size_t max_lds) {
-    const void* kernels[] = {reinterpret_cast<const void*>(&trace_kernel<true, true>),
-                             reinterpret_cast<const void*>(&trace_kernel<true, false>),
-                             reinterpret_cast<const void*>(&trace_kernel<false, true>),
-                             reinterpret_cast<const void*>(&trace_kernel<false, false>),
-                             reinterpret_cast<const void*>(&trace_kernel<true, true, true>),
-                             reinterpret_cast<const void*>(&trace_kernel<true, true, false, true>),
-                             reinterpret_cast<const void*>(&trace_kernel<false, true, false, true>),
-                             reinterpret_cast<const void*>(&trace_kernel<true, true, true, true>)};
-    for (const void* k : kernels) {
-        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds);
+    const auto set = [&](auto* k) {
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds);
+    };
+    for (int v = 0; v < 32; ++v) {
+        const hipError_t e = with_kernel((v & 1) != 0, (v & 2) != 0, (v & 4) != 0, (v & 8) != 0, (v & 16) != 0, set);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -1297,44 +1361,20 @@ hipError_t prepare_trace(size_t max_lds) {
 hipError_t launch_trace(const TraceArgs& a, const LaunchCfg& c, hipStream_t stream, const unsigned char* inline_tab,
                         size_t inline_bytes) {
     const dim3 grid(c.blocks), block(c.waves_per_block * 64);
-    if (inline_tab) {
-        if (!a.sort_cand || a.jobs || inline_bytes > kInlineTableBytes) return hipErrorInvalidValue;
-        TraceArgsInline ai{};
-        static_cast<TraceArgs&>(ai) = a;
-        std::memcpy(ai.inline_tab, inline_tab, inline_bytes);
-        hipLaunchKernelGGL((trace_kernel<true, true, true>), grid, block, c.lds_bytes, stream, ai);
+    const bool count = a.counts != nullptr;
+    if (count && (a.jobs || a.hdr)) return hipErrorInvalidValue;
+    if (inline_tab && (!a.sort_cand || a.jobs || inline_bytes > kInlineTableBytes)) return hipErrorInvalidValue;
+    return with_kernel(a.wide != 0, a.sort_cand != 0, !a.jobs, inline_tab != nullptr, count, [&](auto* k) {
+        if constexpr (std::is_invocable_v<decltype(k), TraceArgsInline> && !std::is_invocable_v<decltype(k), TraceArgs>) {
+            TraceArgsInline ai{};
+            static_cast<TraceArgs&>(ai) = a;
+            std::memcpy(ai.inline_tab, inline_tab, inline_bytes);
+            hipLaunchKernelGGL(k, grid, block, c.lds_bytes, stream, ai);
+        } else {
+            hipLaunchKernelGGL(k, grid, block, c.lds_bytes, stream, a);
+        }
         return hipGetLastError();
-    }
-    if (a.sort_cand) {
-        if (!a.jobs)
-            hipLaunchKernelGGL((trace_kernel<true, true>), grid, block, c.lds_bytes, stream, a);
-        else
-            hipLaunchKernelGGL((trace_kernel<true, false>), grid, block, c.lds_bytes, stream, a);
-    } else {
-        if (!a.jobs)
-            hipLaunchKernelGGL((trace_kernel<false, true>), grid, block, c.lds_bytes, stream, a);
-        else
-            hipLaunchKernelGGL((trace_kernel<false, false>), grid, block, c.lds_bytes, stream, a);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_trace_counted(const TraceArgs& a, const LaunchCfg& c, hipStream_t stream,
-                                const unsigned char* inline_tab, size_t inline_bytes) {
-    const dim3 grid(c.blocks), block(c.waves_per_block * 64);
-    if (!a.counts || a.jobs || a.hdr) return hipErrorInvalidValue;
-    if (inline_tab) {
-        if (!a.sort_cand || inline_bytes > kInlineTableBytes) return hipErrorInvalidValue;
-        TraceArgsInline ai{};
-        static_cast<TraceArgs&>(ai) = a;
-        std::memcpy(ai.inline_tab, inline_tab, inline_bytes);
-        hipLaunchKernelGGL((trace_kernel<true, true, true, true>), grid, block, c.lds_bytes, stream, ai);
-    } else if (a.sort_cand) {
-        hipLaunchKernelGGL((trace_kernel<true, true, false, true>), grid, block, c.lds_bytes, stream, a);
-    } else {
-        hipLaunchKernelGGL((trace_kernel<false, true, false, true>), grid, block, c.lds_bytes, stream, a);
-    }
-    return hipGetLastError();
+    });
 }
 
 }  // namespace svo
