@@ -1079,6 +1079,7 @@ size_t fit_lds(const svo_ctx* ctx, svo::TraceArgs& a, uint32_t& waves) {
 int launch(svo_ctx* ctx, const svo_config& cfg, svo::TraceArgs& a, hipStream_t st, const unsigned char* inline_tab = nullptr,
            size_t inline_bytes = 0) {
     a.tile_stride = tile_stride((a.n_rays + 63) / 64);
+    a.tile_inv = 1.0 / (double)((a.n_rays + 63) / 64);
     svo_config c = cfg;
     const size_t lds = fit_lds(ctx, a, c.waves_per_block);
     if (lds > ctx->max_lds) return fail(SVO_ERANGE, "launch needs %zu bytes of LDS per work-group", lds);
@@ -1752,6 +1753,7 @@ int svo_plan_set_jobs(svo_ctx* ctx, svo_plan* plan, const svo_job* jobs, uint32_
         svo::LaunchHdr hdr{};
         hdr.n_rays = P.total;
         hdr.tile_stride = tile_stride((P.total + 63) / 64);
+        hdr.tile_inv = P.total ? 1.0 / (double)((P.total + 63) / 64) : 0.0;
         hdr.n_jobs = (uint32_t)P.jobs.size();
         hdr.n_frames = P.frames;
         hdr.n_cand_total = P.cands;

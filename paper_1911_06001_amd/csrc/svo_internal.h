@@ -111,9 +111,10 @@ constexpr uint32_t kMaxJobs = 256;
 // 128-byte line, then a bitmap of exhausted partitions, then the
 // finished-work-group counter.  Claims are interleaved over the partitions
 // (claim slot s belongs to partition s mod kQueueParts) so that no single
-// address serialises them; a wave starts on its own partition, and a wave
-// that finds a partition dry marks it in the bitmap and moves on to the next
-// partition the bitmap still shows as open.
+// address serialises them; a wave starts on its own partition with a claim
+// that needs no counter, the wave that takes a partition's last claim marks
+// it in the bitmap, and a wave that finds a partition dry moves on to the
+// next one the bitmap still shows as open.
 constexpr uint32_t kQueueParts = 64;
 constexpr uint32_t kQueueStride = 32;                              // uint32 words between counters
 constexpr uint32_t kQueueDry = kQueueParts * kQueueStride;         // 2 words: bitmap of dry partitions
@@ -210,7 +211,9 @@ struct alignas(16) LaunchHdr {
     uint32_t n_cand_total;        // <= TraceArgs::n_cand_total
     uint32_t lds_nodes;           // <= TraceArgs::lds_nodes, even
     uint32_t n_bvh_total;         // <= TraceArgs::n_bvh_total
-    uint32_t pad[5];
+    uint32_t pad0;
+    double tile_inv;              // as TraceArgs::tile_inv
+    uint32_t pad[2];
 };
 static_assert(sizeof(LaunchHdr) == 64, "launch header must be 64 bytes");
 
@@ -229,7 +232,7 @@ constexpr uint32_t kExactMapDoubles = 12;
 
 // In a plan launch (hdr != nullptr) n_jobs, n_frames, n_cand_total,
 // n_bvh_total and lds_nodes are capacities that size the LDS layout, and the header holds
-// the counts; n_rays, tile_stride and cache_src are ignored.
+// the counts; n_rays, tile_stride, tile_inv and cache_src are ignored.
 struct TraceArgs {
     const LaunchHdr* hdr;     // plan launches: counts in device memory; else nullptr
     const JobRec* jobs;       // device job table, or nullptr: the single job in job0
@@ -258,6 +261,7 @@ struct TraceArgs {
     uint32_t reuse;           // 1: the outputs hold the previous trace of these rays (hit buffer)
     unsigned long long* retraced;  // reuse: rays traced again are added here (nullable)
     uint64_t tile_stride;     // claim i covers tile (i * tile_stride) mod tiles (coprime: a permutation)
+    double tile_inv;          // 1 / tiles
     uint32_t step_limit;
     // slow tiles first (one-job launches with whole-tile refill; nullptr:
     // plain order): this queue's state (kHotWords), the target count of

@@ -163,6 +163,14 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)r);
 }
 
+// Wait until this wave's memory operations, atomics without a result among
+// them, have completed.
+__device__ __forceinline__ void wait_memory() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+}
+
 // The slow-tile state's address from a work-group's LDS header.
 __device__ __forceinline__ uint32_t* lds_hot_ptr(const uint32_t* lds_hot) {
     return reinterpret_cast<uint32_t*>((uint64_t)lds_hot[kHotLdsPtr] | ((uint64_t)lds_hot[kHotLdsPtr + 1] << 32));
@@ -394,11 +402,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     uint32_t n_jobs = a.n_jobs, n_frames = a.n_frames, n_cand_total = a.n_cand_total, fill_nodes = a.lds_nodes;
     uint32_t n_bvh = a.n_bvh_total;
     const uint64_t* cache_src = a.cache_src;
-    uint64_t tstride = a.tile_stride;
+    uint32_t tstride = (uint32_t)a.tile_stride;
+    double tile_inv = a.tile_inv;
     if (a.hdr) {
         const LaunchHdr& h = *a.hdr;
         n_rays = h.n_rays;
-        tstride = h.tile_stride;
+        tstride = (uint32_t)h.tile_stride;
+        tile_inv = h.tile_inv;
         n_jobs = min(h.n_jobs, a.n_jobs);
         n_frames = min(h.n_frames, a.n_frames);
         n_cand_total = min(h.n_cand_total, a.n_cand_total);
@@ -411,7 +421,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     // work-groups beyond what this launch's rays need (a plan's grid is
     // fixed) fill no LDS and claim nothing
     const uint32_t wpb = blockDim.x >> 6;
-    const uint32_t n_active = (uint32_t)min((uint64_t)gridDim.x, (((n_rays + 63) >> 6) + wpb - 1) / wpb);
+    const uint32_t n_tiles = (uint32_t)((n_rays + 63) >> 6);   // at most 0xff000000 / 64
+    const uint32_t n_active = min(gridDim.x, (n_tiles + wpb - 1u) / wpb);
     const bool active = blockIdx.x < n_active;
     if (!active) {
         fill_nodes = 0;
@@ -460,12 +471,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     // into its LDS header; the main loop reads the header there and the
     // state's pointer from the arguments, which keeps them out of its scalar
     // registers.
-    const uint64_t n_tiles = (n_rays + 63) >> 6;
     if (kSingle && threadIdx.x < kHotLdsHdr) {
         const uint32_t* hot = a.hot;
         const uint32_t t = threadIdx.x;
         uint32_t v = 0;
-        if (hot && !a.hdr && n_tiles <= kHotMaxTiles) {
+        // (a launch with a tile or less per wave starts them all at once: no
+        // order to choose, and its fixed claims need no queue)
+        if (hot && !a.hdr && n_tiles <= kHotMaxTiles && n_tiles > n_active * wpb) {
             // one round of loads: the words of both lists, then the input's
             const uint32_t b = hot_in(hot);
             if (t == kHotLdsOn) {
@@ -498,12 +510,49 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     __syncthreads();
 
     const uint32_t refill = a.refill;
-    const uint32_t claim = a.claim;
-    // partition-local ray indices run to part_len (whole tiles); a wave owns
-    // the claimed range [rlo, rhi) of partition q (wave-uniform state)
-    const uint32_t part_len = (uint32_t)((n_tiles + kQueueParts - 1) / kQueueParts) * 64u;
-    uint32_t q = (blockIdx.x * wpb + wave) % kQueueParts, rlo = 0, rhi = 0;
-    uint64_t known_dry = 0;  // partitions this wave knows to be dry
+    // partition q holds the claim slots s with s mod kQueueParts == q, so its
+    // partition-local ray indices run to part_len(q) (whole tiles); a wave
+    // owns the claimed range [rlo, rhi) of partition q (wave-uniform state).
+    // Launches with fewer than two tiles per wave claim single tiles, so that
+    // no wave waits for a second one while others have none.
+    const uint32_t n_waves = n_active * wpb;
+    const uint32_t claim = n_tiles < 2u * n_waves ? 64u : a.claim;
+    auto part_len = [&](uint32_t p) -> uint32_t {
+        return (n_tiles / kQueueParts + (p < n_tiles % kQueueParts ? 1u : 0u)) * 64u;
+    };
+    const uint32_t wave_id = blockIdx.x * wpb + wave;
+    uint32_t q = wave_id % kQueueParts, rlo = 0, rhi = 0;
+    // A wave's first claim is fixed: claim wave_id / kQueueParts of its own
+    // partition, and the counters count on from the fixed ones.  Without it
+    // every wave of the grid starts with an atomic on one of 64 addresses,
+    // and a small launch spends its time finding each partition dry: a
+    // launch of 100 invalid rays took 70 us, one atomic round trip per
+    // partition, and takes 5 us.  Launches
+    // that deal out a list of slow tiles start with that instead: a wave may
+    // then spend long on its first tile, and a fixed claim would wait for it.
+    const bool fixed = !(kSingle && lds_hot[kHotLdsDeal] != 0u);
+    auto fixed_len = [&](uint32_t p) -> uint32_t {
+        return fixed ? (n_waves / kQueueParts + (p < n_waves % kQueueParts ? 1u : 0u)) * claim : 0u;
+    };
+    if (fixed) {
+        rhi = part_len(q);
+        rlo = min(wave_id / kQueueParts * claim, rhi);
+        rhi = min(rlo + claim, rhi);
+    }
+    // partitions this wave knows to be dry: here those that the fixed claims
+    // cover (one lane per partition)
+    uint64_t known_dry = __ballot(fixed_len(lane) >= part_len(lane));
+    const bool queue_used = known_dry != ~0ull;   // launch-wide: some partition has claims left
+    // The tile that claim slot s covers: (s tstride) mod n_tiles, exactly (the
+    // product stays below 2^53 and the quotient is off by at most one), in 15
+    // instructions where the integer remainder takes about 80.
+    auto tile_of = [&](uint32_t s) -> uint32_t {
+        const double x = (double)s * (double)tstride;
+        double rem = fma(-trunc(x * tile_inv), (double)n_tiles, x);
+        if (rem < 0.0) rem += (double)n_tiles;
+        if (rem >= (double)n_tiles) rem -= (double)n_tiles;
+        return (uint32_t)rem;
+    };
 
     // per-lane state
     uint32_t mode = M_DONE;
@@ -769,24 +818,28 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
                 else __builtin_amdgcn_s_setprio(0);
             }
             if (!got_hot && rlo >= rhi) {
-                // claim the next range of partition q.  A dry partition is
-                // marked in the shared bitmap by the first wave to overflow
-                // it, so a set bit always means dry (an unset one may be
-                // stale); the wave moves on to the next partition it does not
-                // know to be dry, and is done once it knows all of them are.
-                uint32_t base = part_len;
+                // claim the next range of partition q.  The wave that takes a
+                // partition's last range marks it in the shared bitmap, so a
+                // set bit always means dry (an unset one may be stale); a wave
+                // that finds its partition dry moves on to the next one it does
+                // not know to be dry, and is done once it knows all of them
+                // are.  (Reading the bitmap beside every claim, which saves a
+                // round trip at the end, made the 1080p terrain 2 % slower.)
+                uint32_t base = 0, len = 0;
                 while (known_dry != ~0ull) {
-                    uint32_t* ctr = a.queue + q * kQueueStride;
-                    if (lane == leader) base = atomicAdd(ctr, claim);
-                    base = __shfl(base, (int)leader);
-                    if (base < part_len) break;
                     uint64_t dry = 0;
+                    len = part_len(q);
                     if (lane == leader) {
                         uint32_t* bm = a.queue + kQueueDry;
-                        if (base < part_len + claim) atomicOr(bm + (q >> 5), 1u << (q & 31u));   // first to overflow
-                        dry = (uint64_t)__hip_atomic_load(bm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) |
-                              ((uint64_t)__hip_atomic_load(bm + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) << 32);
+                        base = fixed_len(q) + atomicAdd(a.queue + q * kQueueStride, claim);
+                        if (base >= len)
+                            dry = (uint64_t)__hip_atomic_load(bm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) |
+                                  ((uint64_t)__hip_atomic_load(bm + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) << 32);
+                        else if (base + claim >= len)
+                            atomicOr(bm + (q >> 5), 1u << (q & 31u));
                     }
+                    base = __shfl(base, (int)leader);
+                    if (base < len) break;
                     known_dry |= __shfl(dry, (int)leader) | (1ull << q);
                     if (known_dry == ~0ull) break;
                     // the next partition after q not known to be dry, cyclically
@@ -798,7 +851,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
                     exhausted = true;
                 } else {
                     rlo = base;
-                    rhi = min(base + claim, part_len);
+                    rhi = min(base + claim, len);
                 }
             }
             const uint32_t take = got_hot ? min(nidle, 64u) : ((rlo < rhi) ? min(nidle, rhi - rlo) : 0u);
@@ -807,22 +860,24 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
             // a regular claim's tile (whole tiles: the same for every lane)
             // and the input bitmap's word for it, tested once the rays'
             // loads are on their way
-            const uint64_t csl = (uint64_t)(first >> 6) * kQueueParts + q;
-            const uint64_t ctile = (csl * tstride) % n_tiles;
+            const uint32_t csl = (first >> 6) * kQueueParts + q;
+            const uint32_t ctile = tile_of(csl);
             uint32_t cword = 0;
             if (take && !got_hot && hin) cword = gld(hot_bits(lds_hot_ptr(lds_hot), lds_hot[kHotLdsIn]), ctile >> 5);
             if (mode == M_DONE) {
                 const uint32_t rank =
                     __builtin_amdgcn_mbcnt_hi((uint32_t)(idle >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)idle, 0u));
                 const uint32_t j = first + rank;
-                const uint64_t slot = (uint64_t)(j >> 6) * kQueueParts + q;     // claim order
+                const uint32_t slot = (j >> 6) * kQueueParts + q;     // claim order
                 uint64_t gidx = n_rays;
                 if (got_hot) {
                     if (rank < take && htile < n_tiles) gidx = (uint64_t)htile * 64u + rank;
                 } else if (rank < take && slot < n_tiles) {
                     // a lane in the claim's first tile (every lane, with
                     // whole tiles) takes its tile from ctile
-                    gidx = ((j >> 6) == (first >> 6) ? ctile : (slot * tstride) % n_tiles) * 64u + (j & 63u);
+                    uint32_t tile = ctile;
+                    if ((j >> 6) != (first >> 6)) tile = tile_of(slot);
+                    gidx = (uint64_t)tile * 64u + (j & 63u);
                 }
                 if (gidx < n_rays) {
                     if constexpr (kCount) {
@@ -934,8 +989,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
             if (hon && take) {
                 // wave-uniform
                 const uint32_t t = got_hot ? (htile < n_tiles ? htile : 0xFFFFFFFFu)
-                                           : ((csl < n_tiles && !((cword >> (ctile & 31u)) & 1u)) ? (uint32_t)ctile
-                                                                                                  : 0xFFFFFFFFu);
+                                           : ((csl < n_tiles && !((cword >> (ctile & 31u)) & 1u)) ? ctile : 0xFFFFFFFFu);
                 cur_tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
             }
             if (a.reuse && a.retraced) {
@@ -1213,7 +1267,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     // the last work-group out resets the queue for the next launch; only
     // work-groups that may claim count (an idle one of a plan's fixed grid
     // touches no counter, and skipping its atomic spares the others a
-    // same-address queue)
+    // same-address queue), and none where the fixed claims were all.  Every
+    // word that another work-group reads here is written by atomics, so all
+    // that has to come before the count is their completion: each wave waits
+    // for its own, and no cache is written back or invalidated (a device
+    // fence here did both once per work-group: 140.0 against 137.3 us per
+    // 1080p terrain frame).
+    wait_memory();
     __syncthreads();
     uint32_t* const hot = (kSingle && lds_hot[kHotLdsOn]) ? a.hot : nullptr;
     const uint32_t hp = hot ? lds_hot[kHotLdsIn] : 0u, ob = hp ^ 1u;
@@ -1234,8 +1294,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
             }
         }
     }
-    if (active && threadIdx.x == 0) {
-        __threadfence();
+    if (active && (queue_used || hot) && threadIdx.x == 0) {
+        wait_memory();
         uint32_t* fin = a.queue + kQueueFinished;
         const uint32_t prev = atomicAdd(fin, 1u);
         const bool last = prev == n_active - 1;
