@@ -307,7 +307,7 @@ struct Scene {
     int cur = 0;                        // table the next trace reads
     uint32_t n_frames = 1;              // 1 + n_slots records per table
     // classification of the current table
-    uint32_t n_cand = 0, stack_levels = 1, nest_levels = 0, n_inline = 0, n_bvh = 0, bvh_depth = 0;
+    uint32_t n_cand = 0, stack_levels = 1, nest_levels = 0, n_inline = 0, n_bvh = 0;
     uint64_t bytes = 0;
     bool tuned = false;                 // svo_tune picked `cfg` for this scene
     svo_config cfg{};
@@ -364,7 +364,7 @@ struct svo_plan {
     svo_config cfg{};
     svo::TraceArgs args{};
     svo::LaunchCfg launch_cfg{};
-    uint32_t max_jobs = 0, max_frames = 0, max_cand = 0, stack_cap = 1, nest_cap = 0, max_bvh = 0, bvh_depth_cap = 0;
+    uint32_t max_jobs = 0, max_frames = 0, max_cand = 0, stack_cap = 1, nest_cap = 0, max_bvh = 0;
     size_t off_jobs = 0, off_frames = 0, off_cand = 0, off_sph = 0, off_x = 0, off_bvh = 0, off_cams = 0, bytes = 0;
     unsigned char* dev = nullptr;
     unsigned char* host = nullptr;
@@ -437,7 +437,8 @@ Scene* find_scene(svo_ctx* ctx, svo_scene h) {
 }
 
 // Layout of a scene's frame table: n_frames records, then the candidate list
-// (n_slots u32), then one bounding sphere (centre xyz, radius) per record,
+// (n_slots u32), then room for one bounding sphere (centre xyz, square of the
+// inflated radius) per record, filled in the list's order,
 // then one exact (FP64) map per record.
 inline size_t cand_offset(uint32_t n_frames) { return (size_t)n_frames * sizeof(svo::FrameRec); }
 inline size_t sphere_offset(uint32_t n_frames, uint32_t n_slots) {
@@ -457,15 +458,8 @@ inline size_t table_size(uint32_t n_frames, uint32_t n_slots) {
 }
 
 struct TableInfo {
-    uint32_t n_cand = 0, stack_levels = 1, nest_levels = 0, n_inline = 0, n_bvh = 0, bvh_depth = 0;
+    uint32_t n_cand = 0, stack_levels = 1, nest_levels = 0, n_inline = 0, n_bvh = 0;
 };
-
-// Levels of the hierarchy bvh_build makes over n candidates (median splits,
-// leaves of at most kBvhLeafMax).
-uint32_t bvh_levels(uint32_t n) {
-    if (n <= svo::kBvhLeafMax) return n ? 1u : 0u;
-    return 1u + std::max(bvh_levels(n / 2), bvh_levels(n - n / 2));
-}
 
 struct BItem {
     double lo[3], hi[3], c[3];
@@ -481,13 +475,11 @@ float round_up_f32(double v) {
     return ((double)f < v) ? std::nextafter(f, INFINITY) : f;
 }
 
-// Median-split hierarchy over items [begin, end), nodes in depth-first
-// order from out[n]; returns the node index.  Boxes are widened by 1e-5 of
-// their extent plus 1e-6 of their magnitude and rounded outward to FP32.
-uint32_t bvh_build(std::vector<BItem>& it, uint32_t begin, uint32_t end, uint32_t level, svo::BvhNode* out,
-                   uint32_t& n, uint32_t& depth) {
+// Median-split hierarchy over items [begin, end), nodes in preorder from
+// out[n].  Boxes are widened by 2e-5 of their extent plus 2e-6 of their
+// magnitude and rounded outward to FP32.
+void bvh_build(std::vector<BItem>& it, uint32_t begin, uint32_t end, svo::BvhNode* out, uint32_t& n) {
     const uint32_t me = n++;
-    depth = std::max(depth, level);
     double lo[3], hi[3], clo[3], chi[3];
     for (int a = 0; a < 3; ++a) {
         lo[a] = clo[a] = INFINITY;
@@ -505,7 +497,7 @@ uint32_t bvh_build(std::vector<BItem>& it, uint32_t begin, uint32_t end, uint32_
         ext = std::max(ext, hi[a] - lo[a]);
         mag = std::max(mag, std::max(std::fabs(lo[a]), std::fabs(hi[a])));
     }
-    const double pad = 1e-5 * ext + 1e-6 * mag;
+    const double pad = 2e-5 * ext + 2e-6 * mag;
     svo::BvhNode& N = out[me];
     for (int a = 0; a < 3; ++a) {
         N.lo[a] = round_down_f32(lo[a] - pad);
@@ -514,7 +506,7 @@ uint32_t bvh_build(std::vector<BItem>& it, uint32_t begin, uint32_t end, uint32_
     if (end - begin <= svo::kBvhLeafMax) {
         N.a = begin;
         N.b = svo::kBvhLeaf | (end - begin);
-        return me;
+        return;
     }
     int axis = 0;
     for (int a = 1; a < 3; ++a)
@@ -522,11 +514,10 @@ uint32_t bvh_build(std::vector<BItem>& it, uint32_t begin, uint32_t end, uint32_
     const uint32_t mid = begin + (end - begin) / 2;
     std::nth_element(it.begin() + begin, it.begin() + mid, it.begin() + end,
                      [axis](const BItem& x, const BItem& y) { return x.c[axis] < y.c[axis]; });
-    const uint32_t L = bvh_build(it, begin, mid, level + 1, out, n, depth);
-    const uint32_t R = bvh_build(it, mid, end, level + 1, out, n, depth);
-    out[me].a = L;
-    out[me].b = R;
-    return me;
+    bvh_build(it, begin, mid, out, n);
+    bvh_build(it, mid, end, out, n);
+    out[me].a = n;
+    out[me].b = 0;
 }
 
 // Compose, invert and pack the frame table into `out` (host): record 0 is
@@ -569,6 +560,7 @@ int build_frames(const Scene& S, const std::vector<Aff>& fwd, unsigned char* out
     std::vector<Aff> world(S.n_slots);
     std::vector<uint32_t> depth(S.n_slots, 0), sbase(S.n_slots, 0);
     std::vector<uint32_t> inline_frames;
+    std::vector<std::array<float, 4>> ball(S.n_slots);   // per slot: centre, radius
     for (uint32_t s : A.order) {
         const int32_t p = A.slot_parent[s];
         world[s] = aff_mul(p < 0 ? aff_identity() : world[p], fwd[s]);
@@ -606,8 +598,7 @@ int build_frames(const Scene& S, const std::vector<Aff>& fwd, unsigned char* out
                 }
                 rad = std::max(rad, std::sqrt(q));
             }
-            for (int r = 0; r < 3; ++r) sph[4 * (1 + s) + r] = (float)c[r];
-            sph[4 * (1 + s) + 3] = (float)rad;
+            ball[s] = {(float)c[0], (float)c[1], (float)c[2], (float)rad};
         }
         // does the moved cell stay inside its static cell (parent frame)?
         double pmin[3], psize;
@@ -676,11 +667,17 @@ int build_frames(const Scene& S, const std::vector<Aff>& fwd, unsigned char* out
             for (int r = 0; r < 3; ++r) b.c[r] = 0.5 * (b.lo[r] + b.hi[r]);
         }
         svo::BvhNode* bn = reinterpret_cast<svo::BvhNode*>(out + bvh_offset(S.n_frames, S.n_slots));
-        uint32_t n = 0, depth = 0;
-        bvh_build(items, 0, T.n_cand, 1, bn, n, depth);
+        uint32_t n = 0;
+        bvh_build(items, 0, T.n_cand, bn, n);
         for (uint32_t i = 0; i < T.n_cand; ++i) cand[i] = items[i].frame;
         T.n_bvh = n;
-        T.bvh_depth = depth;
+    }
+    // spheres in list order, the radius as its inflated square
+    for (uint32_t k = 0; k < T.n_cand + T.n_inline; ++k) {
+        const std::array<float, 4>& b = ball[cand[k] - 1];
+        const float r = b[3] * 1.0001f;
+        for (int a = 0; a < 3; ++a) sph[4 * k + a] = b[a];
+        sph[4 * k + 3] = r * r;
     }
     return SVO_OK;
 }
@@ -715,7 +712,6 @@ int upload_frames(Scene& S, hipStream_t stream, bool to_device) {
     S.nest_levels = T.nest_levels;
     S.n_inline = T.n_inline;
     S.n_bvh = T.n_bvh;
-    S.bvh_depth = T.bvh_depth;
     return SVO_OK;
 }
 
@@ -1167,7 +1163,7 @@ uint32_t child_mask(const Scene& S) { return wide_pool(S) ? ~0u : ~svo::kNodeFar
 struct Packing {
     std::vector<PackedJob> jobs;        // non-empty jobs, in order
     uint64_t total = 0;
-    uint32_t frames = 0, cands = 0, max_cand = 0, stack_levels = 1, nest_levels = 0, bvh = 0, bvh_depth = 0;
+    uint32_t frames = 0, cands = 0, max_cand = 0, stack_levels = 1, nest_levels = 0, bvh = 0;
     const uint64_t* cache_src = nullptr;  // the pool with the most rays
     bool wide = false;                  // some pool is wide
 };
@@ -1215,13 +1211,11 @@ int pack_jobs(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, const std::set
             Q.T.stack_levels = S->stack_levels;
             Q.T.nest_levels = S->nest_levels;
             Q.T.n_bvh = S->n_bvh;
-            Q.T.bvh_depth = S->bvh_depth;
             Q.T.n_inline = S->n_inline;
         }
         P.frames += S->n_frames;
         P.cands += Q.T.n_cand + Q.T.n_inline;
         P.bvh += Q.T.n_bvh;
-        P.bvh_depth = std::max(P.bvh_depth, Q.T.bvh_depth);
         P.total += J.n;
         if (P.total > 0xFF000000ull) return fail(SVO_ERANGE, "at most 0xff000000 rays per launch");
         P.max_cand = std::max(P.max_cand, Q.T.n_cand);
@@ -1327,7 +1321,6 @@ int trace_rays(svo_ctx* ctx, svo_scene scene, const float* rays, uint64_t n, uin
     // path whatever the count (such scenes have at most 10 slots)
     const bool sorted = S->n_cand <= sort_limit(cfg) || !S->dev_current;
     a.n_bvh_total = sorted ? 0u : S->n_bvh;
-    a.bvh_depth = S->bvh_depth;
     // transforms changed since the device table was written: the table
     // travels in the arguments
     const unsigned char* tab = nullptr;
@@ -1507,7 +1500,6 @@ int trace_batch(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, void* stream
         svo::TraceArgs a{};
         const bool sorted = P.max_cand <= sort_limit(cfg);
         a.n_bvh_total = sorted ? 0u : P.bvh;
-        a.bvh_depth = P.bvh_depth;
         a.n_jobs = (uint32_t)P.jobs.size();
         a.n_frames = P.frames;
         a.n_cand_total = P.cands;
@@ -1673,7 +1665,6 @@ int svo_plan_create(svo_ctx* ctx, const svo_scene* scenes, uint32_t n_scenes, co
         pl->off_x = pl->off_sph + (size_t)pl->max_frames * 16;
         pl->off_bvh = pl->off_x + (size_t)pl->max_frames * kXmapBytes;
         pl->max_bvh = pl->max_cand > sort_limit(pl->cfg) ? 2 * pl->max_frames : 0u;
-        pl->bvh_depth_cap = bvh_levels(pl->max_cand);
         pl->off_cams = pl->off_bvh + (size_t)pl->max_bvh * sizeof(svo::BvhNode);
         pl->bytes = pl->off_cams + (size_t)pl->max_jobs * sizeof(svo::CameraArgs);
 
@@ -1685,7 +1676,6 @@ int svo_plan_create(svo_ctx* ctx, const svo_scene* scenes, uint32_t n_scenes, co
         a.n_frames = pl->max_frames;
         a.n_cand_total = pl->max_frames;
         a.n_bvh_total = pl->max_bvh;
-        a.bvh_depth = pl->bvh_depth_cap;
         a.max_cand = pl->max_cand;
         a.sort_cand = pl->max_cand <= sort_limit(pl->cfg) ? 1u : 0u;
         a.stack_levels = pl->stack_cap;
@@ -1742,7 +1732,7 @@ int svo_plan_set_jobs(svo_ctx* ctx, svo_plan* plan, const svo_job* jobs, uint32_
         if (P.frames > plan->max_frames)
             return fail(SVO_ERANGE, "%u frame records, the plan holds %u", P.frames, plan->max_frames);
         if (P.stack_levels > plan->stack_cap || P.nest_levels > plan->nest_cap || P.max_cand > plan->max_cand ||
-            (plan->max_bvh && P.bvh > plan->max_bvh) || P.bvh_depth > plan->bvh_depth_cap)
+            (plan->max_bvh && P.bvh > plan->max_bvh))
             return fail(SVO_ERANGE, "jobs exceed the plan's stack, nesting or candidate capacity");
         if (plan->ev_pending) {
             HIP_TRY(hipSetDevice(ctx->device));

@@ -49,15 +49,20 @@ constexpr uint32_t kNodeFarWide = 0x100u;
 
 // Frames entered in place may nest this deep inside one top-level frame.
 constexpr uint32_t kMaxInlineNest = 4;
-// Per-lane candidate entry tables are kept in LDS up to this many candidates;
-// beyond, candidates are found through a bounding-box hierarchy.
+// Candidates are tested one by one up to this many; beyond, they are found
+// through a bounding-box hierarchy.
 constexpr uint32_t kMaxSortedCand = 16;
+// A ray's list of candidates to walk holds this many at a time; an entry's
+// low bits are the candidate's place in its job's list (at most 1022).
+constexpr uint32_t kCandList = 8;
+constexpr uint32_t kCandIndexMask = 0x7FFu;
 
-// One node of a frame table's hierarchy over its candidate frames: the
-// world-space box of the moved root cells below it (widened outward so that
-// FP32 slab tests never lose a hit).  Interior: a = left child, b = right
-// child (node indices within the table's hierarchy).  Leaf: b = kBvhLeaf |
-// count, a = first entry in the table's candidate list.  32 bytes.
+// One node of a frame table's hierarchy over its candidate frames, in
+// preorder: the world-space box of the moved root cells below it (widened
+// outward so that FP32 slab tests never lose a hit).  Interior: a = the node
+// after its subtree, b = 0 (its children follow it).  Leaf: b = kBvhLeaf |
+// count, a = first entry in the table's candidate list; leaves come in list
+// order.  32 bytes.
 struct alignas(16) BvhNode {
     float lo[3];
     uint32_t a;
@@ -239,11 +244,11 @@ struct TraceArgs {
     JobRec job0;
     const FrameRec* frames;   // n_frames records; job j's slot s is frames[frame_base_j + 1 + s]
     const uint32_t* cand;     // candidate frames (absolute indices), per job contiguous
-    const float4* spheres;    // n_frames world bounding spheres (centre, radius) of the moved root cells
+    const float4* spheres;    // per job, n_frames entries: world bounding spheres of the moved root cells of the job's
+                              // listed frames, in list order (centre, square of the radius inflated by 1e-4)
     const double* xmaps;      // n_frames exact maps (kExactMapDoubles each), indexed like frames
     const BvhNode* bvh;       // n_bvh_total hierarchy nodes, per job contiguous (job j's root at bvh_base_j)
     uint32_t n_bvh_total;
-    uint32_t bvh_depth;       // hierarchy stack entries per lane (used when sort_cand == 0)
     uint32_t n_jobs;
     uint32_t n_frames;
     uint32_t n_cand_total;
@@ -255,7 +260,7 @@ struct TraceArgs {
     uint32_t stack_levels;    // traversal stack entries per lane
     uint32_t nest_levels;     // frame stack entries per lane (inline frames)
     uint32_t wide;            // 1: some pool has more than kPackedNodes nodes
-    uint32_t sort_cand;       // 1: candidates in entry order via a per-lane LDS table
+    uint32_t sort_cand;       // 1: candidates tested one by one, 0: through the hierarchy
     uint32_t refill;          // a wave claims new rays once this many lanes are idle (1..64)
     uint32_t claim;           // rays a wave takes from a partition counter at once (a multiple of 64)
     uint32_t reuse;           // 1: the outputs hold the previous trace of these rays (hit buffer)

@@ -17,10 +17,12 @@
 //      cell, switch into that node's frame in place (Sec. 3, Fig. 1: the ray,
 //      not the model, is transformed) and resume the enclosing walk after it;
 //   5. transformed subtrees that leave their static cell are candidates,
-//      traced from their own roots and skipped once their entry lies beyond
-//      the best hit (the depth sort of Sec. 4.2): up to 16 in order of exact
-//      root-cell entry after the bounding-sphere test of Sec. 4.1, more
-//      through a hierarchy of their world boxes, nearer boxes first;
+//      traced from their own roots in order of root-cell entry and skipped
+//      once it lies beyond the best hit (the depth sort of Sec. 4.2): after
+//      the walk of the world frame each ray lists those that it may enter
+//      before its hit, by the bounding-sphere test of Sec. 4.1 and the slab
+//      entry, up to 16 tested one by one, more through a hierarchy of their
+//      world boxes;
 //   6. at the hit, recompute its entry t and face from the frame's FP64 map
 //      (the walk's FP32 entry t carries an error that grows with the
 //      coordinates); write id, slot, t and the normal (entry face, inverse
@@ -249,43 +251,68 @@ __device__ __forceinline__ bool exact_hit(const double* X, const Ray& r, const F
 // for FP32: false only when the ray segment [tmin, tlimit] certainly misses
 // the sphere (its perpendicular distance exceeds the radius, or the sphere
 // lies wholly before tmin or after tlimit).  To absorb rounding the radius
-// is inflated by a relative 1e-4, and its square by 1e-6 of the squared
-// centre distance (about 1e-3 of the distance).
+// is inflated by a relative 1e-4 (sp.w is its square), and that square by
+// 1e-6 of the squared centre distance (about 1e-3 of the distance).  A miss
+// costs 13 instructions.
 __device__ __forceinline__ bool sphere_may_hit(const float4 sp, const Ray& r, float tlimit) {
     const float lx = sp.x - r.ox, ly = sp.y - r.oy, lz = sp.z - r.oz;
-    const float dd = fmaf(r.dx, r.dx, fmaf(r.dy, r.dy, r.dz * r.dz));
+    const float idd = rcp_fast(fmaf(r.dx, r.dx, fmaf(r.dy, r.dy, r.dz * r.dz)));
     const float ll = fmaf(lx, lx, fmaf(ly, ly, lz * lz));
     const float tca = fmaf(lx, r.dx, fmaf(ly, r.dy, lz * r.dz));
-    const float rr = sp.w * 1.0001f;
-    const float r2 = fmaf(rr, rr, 1e-6f * ll);
-    const float idd = rcp_fast(dd);
-    const float perp2 = ll - tca * tca * idd;           // squared distance of the line from the centre
-    if (perp2 > r2) return false;
-    const float half = sqrt_fast(fmaxf(r2 - perp2, 0.f) * idd);  // half chord, in t
-    const float tc = tca * idd;                                    // t of the closest approach
+    const float tc = tca * idd;                            // t of the closest approach
+    const float perp2 = fmaf(-tca, tc, ll * (1.f - 1e-6f)); // squared distance of the line, less the slack
+    if (perp2 > sp.w) return false;
+    const float half = sqrt_fast(fmaxf(sp.w - perp2, 0.f) * idd);  // half chord, in t
     return (tc - half <= tlimit) && (tc + half >= r.tmin);
 }
 
-// Entry t of the ray into a hierarchy box over [tmin, tlimit], +inf when the
-// box is missed or entered beyond tlimit (i*: inverse world direction).
-__device__ __forceinline__ float box_entry(const BvhNode& B, const Ray& r, float ix, float iy, float iz,
-                                           float tlimit) {
-    const float ax = (B.lo[0] - r.ox) * ix, bx = (B.hi[0] - r.ox) * ix;
-    const float ay = (B.lo[1] - r.oy) * iy, by = (B.hi[1] - r.oy) * iy;
-    const float az = (B.lo[2] - r.oz) * iz, bz = (B.hi[2] - r.oz) * iz;
-    const float t0 = fmaxf(max3f(fminf(ax, bx), fminf(ay, by), fminf(az, bz)), r.tmin);
-    const float t1 = fminf(min3f(fmaxf(ax, bx), fmaxf(ay, by), fmaxf(az, bz)), tlimit);
-    return (t0 <= t1) ? t0 : INFINITY;
+// A ray's inverse world direction and -origin times it, for box tests; tiny
+// components clamped as in frame_setup (so no 0 * inf).
+struct BoxRay {
+    float ix, iy, iz, nx, ny, nz;
+};
+
+__device__ __forceinline__ BoxRay box_ray(const Ray& r) {
+    const float eps = max3f(fabsf(r.dx), fabsf(r.dy), fabsf(r.dz)) * 0x1p-21f;
+    BoxRay b;
+    b.ix = rcp_fast(fabsf(r.dx) < eps ? copysignf(eps, r.dx) : r.dx);
+    b.iy = rcp_fast(fabsf(r.dy) < eps ? copysignf(eps, r.dy) : r.dy);
+    b.iz = rcp_fast(fabsf(r.dz) < eps ? copysignf(eps, r.dz) : r.dz);
+    b.nx = -r.ox * b.ix;
+    b.ny = -r.oy * b.iy;
+    b.nz = -r.oz * b.iz;
+    return b;
 }
 
-// Inverse world direction for the hierarchy's box tests, tiny components
-// clamped as in frame_setup (so no 0 * inf).
-__device__ __forceinline__ void inv_world_dir(const Ray& r, float& ix, float& iy, float& iz) {
-    const float eps = max3f(fabsf(r.dx), fabsf(r.dy), fabsf(r.dz)) * 0x1p-21f;
-    ix = rcp_fast(fabsf(r.dx) < eps ? copysignf(eps, r.dx) : r.dx);
-    iy = rcp_fast(fabsf(r.dy) < eps ? copysignf(eps, r.dy) : r.dy);
-    iz = rcp_fast(fabsf(r.dz) < eps ? copysignf(eps, r.dz) : r.dz);
+// Whether the ray meets a hierarchy box within [tmin, tlimit].  The planes'
+// t are off by a few ulp of the origin's and the box's coordinates; the
+// boxes are widened by more (bvh_build).
+__device__ __forceinline__ bool box_hit(const BvhNode& B, const BoxRay& b, float tmin, float tlimit) {
+    const float ax = fmaf(B.lo[0], b.ix, b.nx), bx = fmaf(B.hi[0], b.ix, b.nx);
+    const float ay = fmaf(B.lo[1], b.iy, b.ny), by = fmaf(B.hi[1], b.iy, b.ny);
+    const float az = fmaf(B.lo[2], b.iz, b.nz), bz = fmaf(B.hi[2], b.iz, b.nz);
+    return fmaxf(max3f(fminf(ax, bx), fminf(ay, by), fminf(az, bz)), tmin) <=
+           fminf(min3f(fmaxf(ax, bx), fmaxf(ay, by), fmaxf(az, bz)), tlimit);
 }
+
+// Nodes of the hierarchy with this root.
+__device__ __forceinline__ uint32_t bvh_end(const BvhNode& root) { return (root.b & kBvhLeaf) ? 1u : root.a; }
+
+// Whether the ray may enter frame F's root cell by tlimit, and then a t0 no
+// later than it does (to rounding): the root clip of frame_setup with the
+// hardware reciprocal, widened by more than the two can differ, so that no
+// frame that a walk would enter is ruled out.
+__device__ __forceinline__ bool may_enter(const FrameRec& F, const Ray& r, float tlimit, float& t0) {
+    FrameRay fr;
+    frame_setup<false>(F, r, tlimit, fr, t0);
+    const float N = (float)(1u << fr.K);
+    const float tx = min3f(fmaf(N, fr.ix, fr.bx), fmaf(N, fr.iy, fr.by), fmaf(N, fr.iz, fr.bz));
+    const float slack = fmaxf(max3f(fabsf(fr.bx), fabsf(fr.by), fabsf(fr.bz)), fabsf(t0)) * 0x1p-19f;
+    return t0 - slack <= fminf(tx, tlimit);
+}
+
+// Whether any active lane's v holds (wave-uniform).
+__device__ __forceinline__ bool wave_any(bool v) { return __ballot(v) != 0ull; }
 
 __device__ __forceinline__ bool ray_valid(const Ray& r) {
     const bool fin = isfinite(r.ox) && isfinite(r.oy) && isfinite(r.oz) && isfinite(r.dx) && isfinite(r.dy) &&
@@ -318,10 +345,10 @@ __device__ __forceinline__ void gst(T* p, uint64_t i, T v) {
 
 }  // namespace
 
-// Per-lane candidate state in LDS: the entry table (sorted path) or the
-// hierarchy stack of box indices, one more than its levels.
-__host__ __device__ __forceinline__ size_t cand_lane_bytes(const TraceArgs& a) {
-    return a.sort_cand ? (size_t)a.max_cand * 4 : (a.max_cand ? (size_t)(a.bvh_depth + 1) * 4 : 0);
+// Per-lane candidate list in LDS: up to kCandList entries (most rays have
+// none to three; one with more lists the rest when these are done).
+__host__ __device__ __forceinline__ uint32_t cand_slots(const TraceArgs& a) {
+    return a.max_cand < kCandList ? a.max_cand : kCandList;
 }
 
 // Traversal-stack slots per lane: slot sb + h holds the node whose children
@@ -335,13 +362,13 @@ size_t trace_lds_bytes(const TraceArgs& a, uint32_t waves_per_block) {
                           align16((size_t)a.n_cand_total * 4) + (size_t)a.n_jobs * sizeof(JobRec) +
                           (size_t)a.n_bvh_total * sizeof(BvhNode) + (a.jobs ? 0 : kHotLdsBytes) +
                           (a.has_cam0 ? sizeof(CameraArgs) : 0);
-    const size_t per_wave = cand_lane_bytes(a) * 64 + align16((size_t)stack_slots(a) * 64 * stack_slot_bytes(a)) +
+    const size_t per_wave = (size_t)cand_slots(a) * 256 + align16((size_t)stack_slots(a) * 64 * stack_slot_bytes(a)) +
                             (size_t)a.nest_levels * 64 * 16;
     return shared + per_wave * waves_per_block;
 }
 
-// kSorted: every job's candidates go through the per-lane entry table (at
-// most 16 of them); otherwise through the per-frame box hierarchy.  A launch
+// kSorted: every job's candidates are tested one by one (at most 16 of
+// them); otherwise through the per-frame box hierarchy.  A launch
 // uses one of the two, and each instantiation carries only its own path,
 // which keeps the sorted one at fewer registers.  The sorted one is compiled
 // for 6 resident waves per SIMD (80 VGPRs): the few values that then go to
@@ -386,15 +413,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     if (a.has_cam0) p += sizeof(CameraArgs);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = threadIdx.x >> 6;
-    const size_t ent_bytes = cand_lane_bytes(a) * 64;
+    const size_t ent_bytes = (size_t)cand_slots(a) * 256;
     const size_t stack_bytes = (size_t)stack_slots(a) * 64 * (kWide ? 5 : 4);
     const size_t per_wave = ent_bytes + stack_bytes + (size_t)a.nest_levels * 64 * 16;
-    const uint32_t bst_cap = a.bvh_depth + 1;
     unsigned char* wp = p + per_wave * wave;
-    float* ent = reinterpret_cast<float*>(wp) + lane;                                   // candidate c at ent[c * 64]
-    // hierarchy stack entry k at bst[k * 64]: a box index; its entry is tested
-    // again when popped, against the best hit by then
-    uint32_t* bst = reinterpret_cast<uint32_t*>(wp) + lane;
+    // candidate list, entry k at lst[k * 64]: a lower bound of the entry t
+    // (its upper 21 bits) and the candidate's place in the job's list, so
+    // that the smallest word is the nearest
+    uint32_t* lst = reinterpret_cast<uint32_t*>(wp) + lane;
     // traversal stack, slot l: the node word at stkc[l * 64]; kWide: the
     // child start there and the child mask at stkm[l * 64]
     uint32_t* stkc = reinterpret_cast<uint32_t*>(wp + ent_bytes) + lane;
@@ -577,10 +603,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     uint32_t best_id = kNone, best_inst = kNone;
     int best_f = -1, best_axis = 3;
     uint32_t steps = 0;
-    // the hierarchy walk over the candidates, packed (a job has at most 1023
-    // candidates): bits 0-10 next item of the current leaf, 11-21 the
-    // leaf's end, 22-31 stack depth
-    uint32_t bws = 0;
+    // the ray's candidates: entries in its list, and the first candidate
+    // not yet tested for it
+    uint32_t n_lst = 0, c_next = 0;
     FrameRay fr{};
     // the current cell: corner (px, py, pz), size 2^h, reached at tc0; pw is
     // the word of its parent node (mask in the low byte, child start above;
@@ -686,15 +711,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     // when there is one) is tested up to the previous hit.
     auto previous_stands = [&]() -> bool {
         // a moved frame can hold a hit no later than tlim only if the ray
-        // enters its root cell by then: the sphere first, then the exact
-        // root-cell entry the walk itself uses (leaf entries never precede it)
-        auto may_reach = [&](uint32_t f, float tlim) -> bool {
-            if (!sphere_may_hit(lds_sph[f], r, tlim)) return false;
-            FrameRay cfr;
+        // enters its root cell by then: the sphere first, then the root-cell
+        // entry (leaf entries never precede it); c: place in the job's list
+        auto may_reach = [&](uint32_t c, float tlim) -> bool {
             float t0;
-            // the walk's own entry test rounds differently: widened so that
-            // no frame a full trace would walk is ruled out here
-            return frame_setup<false>(lds_frames[f], r, tlim + fabsf(tlim) * 0x1p-18f, cfr, t0);
+            return sphere_may_hit(lds_sph[fbase + c], r, tlim) && may_enter(lds_frames[lds_cand[cbase + c]], r, tlim, t0);
         };
         const JobRec& J = lds_jobs[job];
         if (!J.out_inst) return false;
@@ -705,31 +726,42 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
         const float tlim = fminf(pt, r.tmax);
         const uint32_t nin = J.n_inline;
         for (uint32_t i = 0; i < nin; ++i)
-            if (may_reach(lds_cand[cbase + ncand + i], tlim)) return false;
+            if (may_reach(ncand + i, tlim)) return false;
         if (ncand == 0) return true;
         if (kSorted) {
             for (uint32_t c = 0; c < ncand; ++c)
-                if (may_reach(lds_cand[cbase + c], tlim)) return false;
+                if (may_reach(c, tlim)) return false;
             return true;
         }
         // any candidate box in front of the previous hit?
-        float ix, iy, iz;
-        inv_world_dir(r, ix, iy, iz);
-        const uint32_t bbase = J.bvh_base;
-        uint32_t sp = 0;
-        if (box_entry(lds_bvh[bbase], r, ix, iy, iz, tlim) < INFINITY) bst[(sp++) * 64] = 0u;
-        while (sp > 0u) {
-            const BvhNode& N = lds_bvh[bbase + bst[(--sp) * 64]];
-            if (N.b & kBvhLeaf) {
-                for (uint32_t c = N.a; c < N.a + (N.b & 0xFFFFu); ++c)
-                    if (may_reach(lds_cand[cbase + c], tlim)) return false;
+        const BoxRay br = box_ray(r);
+        const BvhNode* bvh = lds_bvh + J.bvh_base;
+        const uint32_t end = bvh_end(bvh[0]);
+        for (uint32_t i = 0; i < end;) {
+            const BvhNode& N = bvh[i];
+            const bool leaf = (N.b & kBvhLeaf) != 0u;
+            if (!box_hit(N, br, r.tmin, tlim)) {
+                i = leaf ? i + 1u : N.a;
                 continue;
             }
-            if (sp + 2u > bst_cap) return false;   // cannot happen (depth bound); trace it then
-            if (box_entry(lds_bvh[bbase + N.a], r, ix, iy, iz, tlim) < INFINITY) bst[(sp++) * 64] = N.a;
-            if (box_entry(lds_bvh[bbase + N.b], r, ix, iy, iz, tlim) < INFINITY) bst[(sp++) * 64] = N.b;
+            if (leaf) {
+                for (uint32_t c = N.a; c < N.a + (N.b & 0xFFFFu); ++c)
+                    if (may_reach(c, tlim)) return false;
+            }
+            ++i;
         }
         return true;
+    };
+
+    // Test candidate c of the job for this ray and list it (the list has
+    // room).  By now the ray has its hit in the frames before, if any, so
+    // candidates behind it drop out.
+    auto list_candidate = [&](uint32_t c) {
+        float t0;
+        if (sphere_may_hit(lds_sph[fbase + c], r, tl) && may_enter(lds_frames[lds_cand[cbase + c]], r, tl, t0)) {
+            lst[n_lst * 64] = (__float_as_uint(fmaxf(t0, 0.f)) & ~kCandIndexMask) | c;
+            ++n_lst;
+        }
     };
 
     auto finish = [&]() {
@@ -952,7 +984,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
                     best_f = -1;
                     best_axis = 3;
                     steps = 0;
-                    bws = 0;
+                    n_lst = c_next = 0;
                     // a tile of the input list was traced by the wave it was dealt to
                     const bool dealt = !got_hot && ((cword >> (ctile & 31u)) & 1u);
                     bool keep = false;
@@ -965,26 +997,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
                     } else {
                         retrace = true;
                         tl = r.tmax;
-                        if (kSorted) {
-                            for (uint32_t c = 0; c < ncand; ++c) {
-                                const uint32_t f = lds_cand[cbase + c];
-                                float e = INFINITY;
-                                if (sphere_may_hit(lds_sph[f], r, tl)) {
-                                    FrameRay cfr;
-                                    float t0;
-                                    if (frame_setup<false>(lds_frames[f], r, tl, cfr, t0)) e = t0;
-                                }
-                                ent[c * 64] = e;
-                            }
-                        } else if (ncand) {
-                            float wix, wiy, wiz;
-                            inv_world_dir(r, wix, wiy, wiz);
-                            const float e = box_entry(lds_bvh[lds_jobs[job].bvh_base], r, wix, wiy, wiz, tl);
-                            if (e < INFINITY) {
-                                bst[0] = 0u;
-                                bws = 1u << 22;
-                            }
-                        }
                         mode = start_frame(fbase) ? M_WALK : M_SELECT;
                     }
                 }
@@ -1212,70 +1224,78 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
                 continue;
             }
             // ------------------------------------------------------ next candidate frame
-            if (kSorted) {
-                float bc = INFINITY;
-                int pick = -1;
-                for (uint32_t c = 0; c < ncand; ++c) {
-                    // consumed and missed candidates hold +inf, which must never
-                    // pass the test even when tl is +inf (no hit yet, tmax = inf)
-                    const float e = ent[c * 64];
-                    if (e < INFINITY && e <= tl && (pick < 0 || e < bc)) {
-                        bc = e;
-                        pick = (int)c;
+            // List the candidates the ray may enter before its best hit (the
+            // first time here, and again where the list was full): each by
+            // its bounding sphere (Sec. 4.1) and its root-cell entry.  Listing
+            // after the walk of the static world instead of when the ray was
+            // claimed lets that hit rule most of them out, and the list stays
+            // short (1080p terrain: 0.08 entries per ray for 8 candidates).
+            if (n_lst == 0u && c_next < ncand) {
+                const uint32_t slots = cand_slots(a);
+                if constexpr (kSorted) {
+                    for (; c_next < ncand && n_lst < slots; ++c_next) list_candidate(c_next);
+                } else {
+                    // The job's box hierarchy in preorder, one node for all
+                    // of the wave's lanes that are here (of the same job) at a
+                    // time: a node that no lane's ray meets is skipped with
+                    // its subtree.  The rays of a tile meet nearly the same
+                    // boxes, so this takes about twice the nodes of the worst
+                    // lane at a quarter of the instructions (one box, read
+                    // once for the wave, no per-lane stack), where a
+                    // traversal per lane tested a node and both its children
+                    // on each of its turns.
+                    for (;;) {
+                        const uint32_t j = kSingle ? 0u : uniform_u32(job);
+                        if (kSingle || job == j) {
+                            const BoxRay br = box_ray(r);
+                            const BvhNode* bvh = lds_bvh + uniform_u32(lds_jobs[j].bvh_base);
+                            const uint32_t end = uniform_u32(bvh_end(bvh[0])), first = c_next;
+                            c_next = ncand;
+                            for (uint32_t i = 0; i < end;) {
+                                const BvhNode& N = bvh[i];
+                                const uint32_t na = uniform_u32(N.a), nb = uniform_u32(N.b);
+                                const bool hit = box_hit(N, br, r.tmin, tl);
+                                const bool leaf = (nb & kBvhLeaf) != 0u;
+                                if (!wave_any(hit)) {
+                                    i = leaf ? i + 1u : na;
+                                    continue;
+                                }
+                                if (leaf) {
+                                    // candidates come in ascending order; the
+                                    // first one that finds the list full is
+                                    // where the next listing starts
+                                    for (uint32_t c = na; c < na + (nb & 0xFFFFu); ++c) {
+                                        if (hit && c >= first && c_next == ncand) {
+                                            if (n_lst < slots) list_candidate(c);
+                                            else c_next = c;
+                                        }
+                                    }
+                                }
+                                ++i;
+                            }
+                            break;
+                        }
                     }
                 }
-                if (pick < 0) {
-                    finish();
-                } else {
-                    ent[pick * 64] = INFINITY;
-                    if (start_frame(lds_cand[cbase + pick])) mode = M_WALK;
-                }
+            }
+            if (n_lst == 0u) {
+                finish();
             } else {
-                // candidates through the job's hierarchy of their world
-                // boxes, nearer child first, each box skipped once its entry
-                // lies beyond the best hit; a leaf's candidates then pass the
-                // sphere test (Sec. 4.1) before their exact root-cell entry
-                const uint32_t bbase = lds_jobs[job].bvh_base;
-                float wix, wiy, wiz;
-                inv_world_dir(r, wix, wiy, wiz);
-                uint32_t leaf_i = bws & 0x7FFu, leaf_end = (bws >> 11) & 0x7FFu, bsp = bws >> 22;
-                bool started = false;
-                while (!started) {
-                    if (leaf_i < leaf_end) {
-                        const uint32_t f = lds_cand[cbase + leaf_i++];
-                        if (sphere_may_hit(lds_sph[f], r, tl)) started = start_frame(f);
-                        continue;
-                    }
-                    if (bsp == 0u) break;
-                    --bsp;
-                    // the box may now lie beyond the best hit
-                    const BvhNode& N = lds_bvh[bbase + bst[bsp * 64]];
-                    if (!(box_entry(N, r, wix, wiy, wiz, tl) < INFINITY)) continue;
-                    if (N.b & kBvhLeaf) {
-                        leaf_i = N.a;
-                        leaf_end = N.a + (N.b & 0xFFFFu);
-                        continue;
-                    }
-                    const float eL = box_entry(lds_bvh[bbase + N.a], r, wix, wiy, wiz, tl);
-                    const float eR = box_entry(lds_bvh[bbase + N.b], r, wix, wiy, wiz, tl);
-                    const bool left_near = eL <= eR;
-                    const float en = left_near ? eL : eR, ef = left_near ? eR : eL;
-                    const uint32_t nn = left_near ? N.a : N.b, nf = left_near ? N.b : N.a;
-                    // the far child first, so the near one is popped next
-                    if (ef < INFINITY && bsp < bst_cap) {
-                        bst[bsp * 64] = nf;
-                        ++bsp;
-                    }
-                    if (en < INFINITY && bsp < bst_cap) {
-                        bst[bsp * 64] = nn;
-                        ++bsp;
+                uint32_t near = lst[0], at = 0;
+                for (uint32_t k = 1; k < n_lst; ++k) {
+                    const uint32_t v = lst[k * 64];
+                    if (v < near) {
+                        near = v;
+                        at = k;
                     }
                 }
-                bws = leaf_i | (leaf_end << 11) | (bsp << 22);
-                if (started) {
+                --n_lst;
+                lst[at * 64] = lst[n_lst * 64];
+                if (__uint_as_float(near & ~kCandIndexMask) > fmaxf(tl, 0.f)) {
+                    n_lst = 0;   // the nearest lies beyond the best hit, and so do the others
+                    if (c_next >= ncand) finish();
+                } else if (start_frame(lds_cand[cbase + (near & kCandIndexMask)])) {
                     mode = M_WALK;
-                } else {
-                    finish();
                 }
             }
         }
