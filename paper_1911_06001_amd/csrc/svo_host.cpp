@@ -1086,6 +1086,7 @@ int launch(svo_ctx* ctx, const svo_config& cfg, svo::TraceArgs& a, hipStream_t s
     const uint64_t want = (tiles + c.waves_per_block - 1) / c.waves_per_block;
     const uint64_t cap = (uint64_t)ctx->n_cu * resident_blocks(ctx, c, lds);
     L.blocks = (uint32_t)std::max<uint64_t>(1, std::min(want, cap));
+    a.max_blocks = (uint32_t)cap;
     L.lds_bytes = lds;
     const hipError_t e = svo::launch_trace(a, L, st, inline_tab, inline_bytes);
     if (e != hipSuccess) return fail(SVO_EDEVICE, "trace launch failed: %s", hipGetErrorString(e));
@@ -1498,7 +1499,12 @@ int trace_batch(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, void* stream
         const size_t cb = bb + (size_t)P.bvh * sizeof(svo::BvhNode);
         const size_t bytes = cb + P.jobs.size() * sizeof(svo::CameraArgs);
         svo::TraceArgs a{};
-        const bool sorted = P.max_cand <= sort_limit(cfg);
+        // one by one or through the hierarchy: what svo_tune found for one
+        // scene alone says little about a launch of several jobs, whose
+        // kernels differ more (a batch of 8 sphere and terrain jobs: 353 us
+        // one by one, 431 us when the terrain's tuning had picked the
+        // hierarchy), so those go by the context's limit
+        const bool sorted = P.max_cand <= sort_limit(P.jobs.size() > 1 ? ctx->cfg : cfg);
         a.n_bvh_total = sorted ? 0u : P.bvh;
         a.n_jobs = (uint32_t)P.jobs.size();
         a.n_frames = P.frames;
@@ -1664,7 +1670,7 @@ int svo_plan_create(svo_ctx* ctx, const svo_scene* scenes, uint32_t n_scenes, co
         pl->off_sph = (pl->off_cand + (size_t)pl->max_frames * sizeof(uint32_t) + 15) & ~(size_t)15;
         pl->off_x = pl->off_sph + (size_t)pl->max_frames * 16;
         pl->off_bvh = pl->off_x + (size_t)pl->max_frames * kXmapBytes;
-        pl->max_bvh = pl->max_cand > sort_limit(pl->cfg) ? 2 * pl->max_frames : 0u;
+        pl->max_bvh = pl->max_cand > sort_limit(ctx->cfg) ? 2 * pl->max_frames : 0u;   // as for a batch of jobs
         pl->off_cams = pl->off_bvh + (size_t)pl->max_bvh * sizeof(svo::BvhNode);
         pl->bytes = pl->off_cams + (size_t)pl->max_jobs * sizeof(svo::CameraArgs);
 
@@ -1677,7 +1683,7 @@ int svo_plan_create(svo_ctx* ctx, const svo_scene* scenes, uint32_t n_scenes, co
         a.n_cand_total = pl->max_frames;
         a.n_bvh_total = pl->max_bvh;
         a.max_cand = pl->max_cand;
-        a.sort_cand = pl->max_cand <= sort_limit(pl->cfg) ? 1u : 0u;
+        a.sort_cand = pl->max_bvh ? 0u : 1u;
         a.stack_levels = pl->stack_cap;
         a.nest_levels = pl->nest_cap;
         a.lds_nodes = (uint32_t)std::min<uint64_t>(pl->cfg.lds_cache_nodes, max_pool) & ~1u;
@@ -1687,6 +1693,7 @@ int svo_plan_create(svo_ctx* ctx, const svo_scene* scenes, uint32_t n_scenes, co
         pl->launch_cfg.waves_per_block = pl->cfg.waves_per_block;
         pl->launch_cfg.blocks = (uint32_t)std::max<uint64_t>(1, (uint64_t)ctx->n_cu * resident_blocks(ctx, pl->cfg, lds));
         pl->launch_cfg.lds_bytes = lds;
+        a.max_blocks = pl->launch_cfg.blocks;
 
         HIP_TRY(hipSetDevice(ctx->device));
         auto release = [&]() { destroy_plan(*pl); };

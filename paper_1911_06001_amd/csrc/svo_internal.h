@@ -259,6 +259,7 @@ struct TraceArgs {
     uint32_t lds_nodes;       // pool prefix cached in LDS (even)
     uint32_t stack_levels;    // traversal stack entries per lane
     uint32_t nest_levels;     // frame stack entries per lane (inline frames)
+    uint32_t max_blocks;      // work-groups of this launch's size that can be resident on the device
     uint32_t wide;            // 1: some pool has more than kPackedNodes nodes
     uint32_t sort_cand;       // 1: candidates tested one by one, 0: through the hierarchy
     uint32_t refill;          // a wave claims new rays once this many lanes are idle (1..64)

@@ -553,15 +553,15 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     };
     const uint32_t wave_id = blockIdx.x * wpb + wave;
     uint32_t q = wave_id % kQueueParts, rlo = 0, rhi = 0;
-    // A wave's first claim is fixed: claim wave_id / kQueueParts of its own
-    // partition, and the counters count on from the fixed ones.  Without it
-    // every wave of the grid starts with an atomic on one of 64 addresses,
-    // and a small launch spends its time finding each partition dry: a
-    // launch of 100 invalid rays took 70 us, one atomic round trip per
-    // partition, and takes 5 us.  Launches
-    // that deal out a list of slow tiles start with that instead: a wave may
-    // then spend long on its first tile, and a fixed claim would wait for it.
-    const bool fixed = !(kSingle && lds_hot[kHotLdsDeal] != 0u);
+    // In a launch of at most half the work-groups that can be resident, a
+    // wave's first claim is fixed: claim wave_id / kQueueParts of its own
+    // partition, and the counters count on from the fixed ones.  Such a launch
+    // is over in the time of a tile or two, and a few atomic round trips (about
+    // 0.8 us each) to claim a tile and to find the rest claimed are a good part
+    // of that (256x256 rays: 30.8 us fixed).  A larger one gains nothing by it,
+    // and where another stream's launch still holds part of the device, its
+    // last work-groups start late: tiles kept for them would wait.
+    const bool fixed = 2u * n_active <= a.max_blocks;
     auto fixed_len = [&](uint32_t p) -> uint32_t {
         return fixed ? (n_waves / kQueueParts + (p < n_waves % kQueueParts ? 1u : 0u)) * claim : 0u;
     };
