@@ -116,13 +116,14 @@ typedef struct {
 
 /* Kernel configuration; svo_tune() picks one, svo_set_config() sets one.
    Zero fields select the library defaults.  A launch whose tables do not
-   fit the device's LDS per work-group under it halves lds_cache_nodes, then
-   lowers waves_per_block (to a multiple of 4, then by one), before it
-   reports SVO_ERANGE; results never depend on the configuration. */
+   fit the device's LDS per work-group under it lowers waves_per_block (to a
+   multiple of 4, then by one), before it reports SVO_ERANGE; results never
+   depend on the configuration. */
 typedef struct {
     uint32_t waves_per_block;   /* 1..16 wavefronts (64 lanes) per work-group */
     uint32_t blocks_per_cu;     /* work-groups per compute unit of the persistent grid (capped by what LDS and 32 waves per CU let reside) */
-    uint32_t lds_cache_nodes;   /* first N pool nodes (the top levels, breadth-first) kept in LDS */
+    uint32_t lds_cache_nodes;   /* accepted (at most 16384) and reported, without effect: every node is read through the
+                                   caches, which is faster than a copy of the pool's first nodes in LDS */
     uint32_t refill_lanes;      /* 0 or 64: a wave takes 64-ray tiles; 1..63: claim new rays once that many lanes are idle */
     uint32_t step_limit;        /* cell advances plus candidate selections per ray before SVO_STEP_LIMIT */
     uint32_t claim_tiles;       /* 64-ray tiles a wave takes from the work queue at once (0: 2; at most 64) */
@@ -230,8 +231,7 @@ int svo_trace_rays(svo_ctx* ctx, svo_scene scene, const float* rays, uint64_t n,
    loads), counts[n + i] = frames walked, counts[2n + i] += 1 per result
    write (exactly 1 when every ray is claimed and written once).  trail:
    nullable device uint32 array of trail_cap * n: trail[k * n + i] = pool
-   index of ray i's k-th node load for k < trail_cap, bit 31 set when it came
-   from the LDS copy of the pool prefix.  Errors: as svo_trace_rays;
+   index of ray i's k-th node load for k < trail_cap.  Errors: as svo_trace_rays;
    SVO_EINVAL without counts, SVO_ERANGE above 2^31 - 1 rays or a trail over
    2^40 entries. */
 int svo_trace_rays_counted(svo_ctx* ctx, svo_scene scene, const float* rays, uint64_t n, uint32_t* out_id,
@@ -384,14 +384,13 @@ typedef struct {
 
 /* Create a plan for jobs on the given scenes (host array of n_scenes >= 1
    handles).  The scenes fix the plan's traversal-stack and frame-nesting
-   capacity (bounds that hold under any transforms), the LDS candidate table
-   and the pool whose prefix is cached in LDS (the first scene's).  The
-   kernel configuration is the first scene's tuned one if it has one, else
+   capacity (bounds that hold under any transforms) and the LDS candidate
+   list.  The kernel configuration is the first scene's tuned one if it has one, else
    the context's.  Allocates a device table, pinned staging of the same
    size and a private work queue (zeroed; synchronous).  Errors: SVO_EINVAL
    (NULL argument, unknown scene, non-zero reserved field), SVO_ERANGE
    (limits out of range, or the plan's LDS footprint exceeds the device's
-   even with no node cache and one wave per work-group), SVO_ENOMEM,
+   even with one wave per work-group), SVO_ENOMEM,
    SVO_EDEVICE.  *out is NULL on
    failure. */
 int svo_plan_create(svo_ctx* ctx, const svo_scene* scenes, uint32_t n_scenes, const svo_plan_limits* limits,
@@ -428,8 +427,7 @@ int svo_set_config(svo_ctx* ctx, const svo_config* cfg);
 
 /* Autotuner.  Times candidate kernel configurations on n device sample rays
    against `scene` under its current transforms, in two stages: the launch
-   shape (waves per work-group, work-groups per CU, LDS pool-prefix size),
-   then lane refill, tiles per work-queue claim and the candidate ordering
+   shape (waves per work-group, work-groups per CU), then lane refill, tiles per work-queue claim and the candidate ordering
    (sorted table or hierarchy) for the fastest shape, then five times longer timings of that winner, the first
    stage's winner and the next two shapes.  Infrastructure: no passage of the paper defines it.  Keeps
    the fastest for that scene -- later svo_trace_rays calls on it use it, and

@@ -1053,17 +1053,13 @@ uint64_t tile_stride(uint64_t tiles) {
     return s ? s : 1;
 }
 
-// Fit a launch into the per-work-group LDS limit: halve the node cache,
-// then take waves out of the work-group (to the next multiple of 4, so the
-// four SIMDs stay evenly loaded, then one at a time).  Results never depend
-// on either; a configuration tuned on one scene may meet a batch whose
-// tables are larger.  Returns the LDS bytes, above the limit if nothing fits.
-size_t fit_lds(const svo_ctx* ctx, svo::TraceArgs& a, uint32_t& waves) {
+// Fit a launch into the per-work-group LDS limit: take waves out of the
+// work-group (to the next multiple of 4, so the four SIMDs stay evenly
+// loaded, then one at a time).  Results never depend on them; a configuration
+// tuned on one scene may meet a batch whose tables are larger.  Returns the
+// LDS bytes, above the limit if nothing fits.
+size_t fit_lds(const svo_ctx* ctx, const svo::TraceArgs& a, uint32_t& waves) {
     size_t lds = svo::trace_lds_bytes(a, waves);
-    while (lds > ctx->max_lds && a.lds_nodes > 0) {
-        a.lds_nodes = (a.lds_nodes / 2) & ~1u;
-        lds = svo::trace_lds_bytes(a, waves);
-    }
     while (lds > ctx->max_lds && waves > 1) {
         waves = (waves > 4 && waves % 4) ? waves & ~3u : (waves > 4 ? waves - 4 : waves - 1);
         lds = svo::trace_lds_bytes(a, waves);
@@ -1079,7 +1075,6 @@ int launch(svo_ctx* ctx, const svo_config& cfg, svo::TraceArgs& a, hipStream_t s
     svo_config c = cfg;
     const size_t lds = fit_lds(ctx, a, c.waves_per_block);
     if (lds > ctx->max_lds) return fail(SVO_ERANGE, "launch needs %zu bytes of LDS per work-group", lds);
-    if (!a.jobs && a.job0.lds_nodes) a.job0.lds_nodes = a.lds_nodes;
     svo::LaunchCfg L{};
     L.waves_per_block = c.waves_per_block;
     const uint64_t tiles = (a.n_rays + 63) / 64;
@@ -1165,7 +1160,7 @@ struct Packing {
     std::vector<PackedJob> jobs;        // non-empty jobs, in order
     uint64_t total = 0;
     uint32_t frames = 0, cands = 0, max_cand = 0, stack_levels = 1, nest_levels = 0, bvh = 0;
-    const uint64_t* cache_src = nullptr;  // the pool with the most rays
+    const Scene* main = nullptr;        // the scene whose pool the most rays walk
     bool wide = false;                  // some pool is wide
 };
 
@@ -1227,10 +1222,10 @@ int pack_jobs(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, const std::set
         P.jobs.push_back(std::move(Q));
     }
     uint64_t best = 0;
-    for (auto& kv : rays_per_pool)
-        if (kv.second > best) {
-            best = kv.second;
-            P.cache_src = kv.first;
+    for (auto& Q : P.jobs)
+        if (rays_per_pool[Q.S->d_nodes] > best) {
+            best = rays_per_pool[Q.S->d_nodes];
+            P.main = Q.S;
         }
     return SVO_OK;
 }
@@ -1238,11 +1233,10 @@ int pack_jobs(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, const std::set
 // Write job records, frame records, candidates (absolute frame indices),
 // spheres, exact maps and hierarchy nodes (skipped when br is null: launches
 // that take every candidate through the sorted path) of a packing into host
-// memory; the jobs of the cached pool get `cache_nodes` LDS nodes.
-// Camera jobs get their camera at cams[i] (host), which the launch reads at
+// memory.  Camera jobs get their camera at cams[i] (host), which the launch reads at
 // dev_cams + i.
 void write_tables(const Packing& P, svo::JobRec* jr, svo::FrameRec* fr, uint32_t* cr, float* sr, double* xr,
-                  svo::BvhNode* br, uint32_t cache_nodes, svo::CameraArgs* cams, const svo::CameraArgs* dev_cams) {
+                  svo::BvhNode* br, svo::CameraArgs* cams, const svo::CameraArgs* dev_cams) {
     uint64_t begin = 0;
     for (size_t i = 0; i < P.jobs.size(); ++i) {
         const PackedJob& Q = P.jobs[i];
@@ -1258,9 +1252,8 @@ void write_tables(const Packing& P, svo::JobRec* jr, svo::FrameRec* fr, uint32_t
             std::memcpy(br + Q.bvh_base, tab + bvh_offset(S.n_frames, S.n_slots), (size_t)Q.T.n_bvh * sizeof(svo::BvhNode));
         const svo_job& J = *Q.j;
         jr[i] = svo::JobRec{S.d_nodes, reinterpret_cast<const float4*>(J.rays), J.out_id, J.out_inst, J.out_t,
-                            J.out_normal, begin, Q.frame_base, Q.cand_base, Q.T.n_cand,
-                            S.d_nodes == P.cache_src ? cache_nodes : 0u, Q.bvh_base, Q.T.n_inline,
-                            Q.has_cam ? dev_cams + i : nullptr, child_mask(S), 0};
+                            J.out_normal, begin, Q.frame_base, Q.cand_base, Q.T.n_cand, Q.bvh_base, Q.T.n_inline,
+                            child_mask(S), Q.has_cam ? dev_cams + i : nullptr, 0};
         if (Q.has_cam) cams[i] = Q.cam;
         begin += J.n;
     }
@@ -1308,10 +1301,9 @@ int trace_rays(svo_ctx* ctx, svo_scene scene, const float* rays, uint64_t n, uin
     HIP_TRY(hipSetDevice(ctx->device));
     svo::TraceArgs a{};
     const svo_config& cfg = S->tuned ? S->cfg : ctx->cfg;
-    const uint32_t cache = (uint32_t)std::min<uint64_t>(cfg.lds_cache_nodes, S->n_nodes) & ~1u;
     a.jobs = nullptr;
     a.job0 = svo::JobRec{S->d_nodes, reinterpret_cast<const float4*>(rays), out_id, out_inst, out_t, out_normal,
-                         0, 0, 0, S->n_cand, cache, 0, S->n_inline};
+                         0, 0, 0, S->n_cand, 0, S->n_inline, child_mask(*S), nullptr, 0};
     a.frames = reinterpret_cast<const svo::FrameRec*>(S->d_table[S->cur]);
     a.cand = reinterpret_cast<const uint32_t*>(S->d_table[S->cur] + cand_offset(S->n_frames));
     a.spheres = reinterpret_cast<const float4*>(S->d_table[S->cur] + sphere_offset(S->n_frames, S->n_slots));
@@ -1338,9 +1330,7 @@ int trace_rays(svo_ctx* ctx, svo_scene scene, const float* rays, uint64_t n, uin
     a.n_cand_total = S->n_cand + S->n_inline;
     a.max_cand = S->n_cand;
     a.n_rays = n;
-    a.cache_src = S->d_nodes;
     a.queue = ctx->d_queue + svo::kQueueWords * qslot;
-    a.lds_nodes = cache;
     a.stack_levels = S->stack_levels;
     a.nest_levels = S->nest_levels;
     a.sort_cand = sorted ? 1u : 0u;
@@ -1480,15 +1470,8 @@ int trace_batch(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, void* stream
         }
         HIP_TRY(hipSetDevice(ctx->device));
 
-        // configuration and node cache: the pool with the most rays in this batch
-        const svo_config* pcfg = &ctx->cfg;
-        uint64_t cache_pool_nodes = 0;
-        for (auto& J : P.jobs)
-            if (J.S->d_nodes == P.cache_src) {
-                cache_pool_nodes = J.S->n_nodes;
-                if (J.S->tuned) pcfg = &J.S->cfg;
-            }
-        svo_config cfg = *pcfg;
+        // configuration: that of the scene with the most rays in this batch
+        svo_config cfg = P.main->tuned ? P.main->cfg : ctx->cfg;
 
         // pack [jobs][frames][candidates][spheres][exact maps][hierarchy nodes][cameras]
         const size_t jb = P.jobs.size() * sizeof(svo::JobRec);
@@ -1511,9 +1494,7 @@ int trace_batch(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, void* stream
         a.n_cand_total = P.cands;
         a.max_cand = P.max_cand;
         a.n_rays = P.total;
-        a.cache_src = P.cache_src;
         a.queue = queue;
-        a.lds_nodes = (uint32_t)std::min<uint64_t>(cfg.lds_cache_nodes, cache_pool_nodes) & ~1u;
         a.sort_cand = sorted ? 1u : 0u;
         a.stack_levels = P.stack_levels;
         a.nest_levels = P.nest_levels;
@@ -1524,7 +1505,6 @@ int trace_batch(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, void* stream
             a.has_cam0 = 1;
             a.cam0 = P.jobs[0].cam;
         }
-        // size LDS now: a smaller node cache changes the jobs' lds_nodes
         const size_t lds = fit_lds(ctx, a, cfg.waves_per_block);
         if (lds > ctx->max_lds) return fail(SVO_ERANGE, "batch needs %zu bytes of LDS per work-group", lds);
 
@@ -1536,7 +1516,7 @@ int trace_batch(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, void* stream
             const svo_job& J = *Q.j;
             a.jobs = nullptr;
             a.job0 = svo::JobRec{S.d_nodes, reinterpret_cast<const float4*>(J.rays), J.out_id, J.out_inst, J.out_t,
-                                 J.out_normal, 0, 0, 0, Q.T.n_cand, a.lds_nodes, 0, Q.T.n_inline};
+                                 J.out_normal, 0, 0, 0, Q.T.n_cand, 0, Q.T.n_inline, child_mask(S), nullptr, 0};
             a.inline_off_cand = (uint32_t)cand_offset(S.n_frames);
             a.inline_off_sph = (uint32_t)sphere_offset(S.n_frames, S.n_slots);
             a.inline_off_x = (uint32_t)xmap_offset(S.n_frames, S.n_slots);
@@ -1555,7 +1535,7 @@ int trace_batch(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, void* stream
             unsigned char* D = ctx->d_static + svo::kStaticQueueBytes;
             write_tables(P, reinterpret_cast<svo::JobRec*>(H), reinterpret_cast<svo::FrameRec*>(H + jb),
                          reinterpret_cast<uint32_t*>(H + jb + fb), reinterpret_cast<float*>(H + sb),
-                         reinterpret_cast<double*>(H + xb), reinterpret_cast<svo::BvhNode*>(H + bb), a.lds_nodes,
+                         reinterpret_cast<double*>(H + xb), reinterpret_cast<svo::BvhNode*>(H + bb),
                          reinterpret_cast<svo::CameraArgs*>(H + cb), reinterpret_cast<const svo::CameraArgs*>(D + cb));
             a.jobs = reinterpret_cast<const svo::JobRec*>(D);
             if (P.jobs.size() == 1) {
@@ -1594,7 +1574,7 @@ int trace_batch(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, void* stream
         if (!B.ev) HIP_TRY(hipEventCreateWithFlags(&B.ev, hipEventDisableTiming));
         write_tables(P, reinterpret_cast<svo::JobRec*>(B.host), reinterpret_cast<svo::FrameRec*>(B.host + jb),
                      reinterpret_cast<uint32_t*>(B.host + jb + fb), reinterpret_cast<float*>(B.host + sb),
-                     reinterpret_cast<double*>(B.host + xb), reinterpret_cast<svo::BvhNode*>(B.host + bb), a.lds_nodes,
+                     reinterpret_cast<double*>(B.host + xb), reinterpret_cast<svo::BvhNode*>(B.host + bb),
                      reinterpret_cast<svo::CameraArgs*>(B.host + cb), reinterpret_cast<const svo::CameraArgs*>(B.dev + cb));
         a.jobs = reinterpret_cast<const svo::JobRec*>(B.dev);
         if (P.jobs.size() == 1) {
@@ -1646,7 +1626,6 @@ int svo_plan_create(svo_ctx* ctx, const svo_scene* scenes, uint32_t n_scenes, co
     try {
         std::unique_ptr<svo_plan> pl(new svo_plan());
         uint32_t max_slots = 0;
-        uint64_t max_pool = 0;
         for (uint32_t i = 0; i < n_scenes; ++i) {
             Scene* S = find_scene(ctx, scenes[i]);
             if (!S) return fail(SVO_EINVAL, "unknown scene %u", scenes[i]);
@@ -1655,7 +1634,6 @@ int svo_plan_create(svo_ctx* ctx, const svo_scene* scenes, uint32_t n_scenes, co
             pl->nest_cap = std::max(pl->nest_cap, std::min<uint32_t>(svo::kMaxInlineNest, S->an.max_nesting));
             if (wide_pool(*S)) pl->args.wide = 1u;
             max_slots = std::max(max_slots, S->n_slots);
-            max_pool = std::max(max_pool, S->n_nodes);
         }
         if (pl->stack_cap > 127) return fail(SVO_ERANGE, "scenes need %u stack levels (limit 127)", pl->stack_cap);
         Scene* S0 = find_scene(ctx, scenes[0]);
@@ -1686,7 +1664,6 @@ int svo_plan_create(svo_ctx* ctx, const svo_scene* scenes, uint32_t n_scenes, co
         a.sort_cand = pl->max_bvh ? 0u : 1u;
         a.stack_levels = pl->stack_cap;
         a.nest_levels = pl->nest_cap;
-        a.lds_nodes = (uint32_t)std::min<uint64_t>(pl->cfg.lds_cache_nodes, max_pool) & ~1u;
         fill_common(pl->cfg, a);
         const size_t lds = fit_lds(ctx, a, pl->cfg.waves_per_block);
         if (lds > ctx->max_lds) return fail(SVO_ERANGE, "plan needs %zu bytes of LDS per work-group", lds);
@@ -1755,15 +1732,10 @@ int svo_plan_set_jobs(svo_ctx* ctx, svo_plan* plan, const svo_job* jobs, uint32_
         hdr.n_frames = P.frames;
         hdr.n_cand_total = P.cands;
         hdr.n_bvh_total = plan->max_bvh ? P.bvh : 0u;
-        uint32_t fill = 0;
-        for (auto& J : P.jobs)
-            if (J.S->d_nodes == P.cache_src) fill = (uint32_t)std::min<uint64_t>(plan->args.lds_nodes, J.S->n_nodes) & ~1u;
-        hdr.cache_src = fill ? P.cache_src : nullptr;
-        hdr.lds_nodes = fill;
         std::memcpy(H, &hdr, sizeof hdr);
         write_tables(P, reinterpret_cast<svo::JobRec*>(H + plan->off_jobs), reinterpret_cast<svo::FrameRec*>(H + plan->off_frames),
                      reinterpret_cast<uint32_t*>(H + plan->off_cand), reinterpret_cast<float*>(H + plan->off_sph),
-                     reinterpret_cast<double*>(H + plan->off_x), plan->max_bvh ? reinterpret_cast<svo::BvhNode*>(H + plan->off_bvh) : nullptr, fill,
+                     reinterpret_cast<double*>(H + plan->off_x), plan->max_bvh ? reinterpret_cast<svo::BvhNode*>(H + plan->off_bvh) : nullptr,
                      reinterpret_cast<svo::CameraArgs*>(H + plan->off_cams),
                      reinterpret_cast<const svo::CameraArgs*>(plan->dev + plan->off_cams));
         return SVO_OK;
@@ -1829,13 +1801,12 @@ int svo_tune(svo_ctx* ctx, svo_scene scene, const float* sample_rays, uint64_t n
     const svo_config was_cfg = S->cfg;
     svo_config win = base;
     float win_ms = 1e30f;
-    // Stages: the launch shape (waves per work-group, work-groups per CU,
-    // LDS node cache) at whole-tile refill and 2-tile claims; refill, claim
+    // Stages: the launch shape (waves per work-group, work-groups per CU)
+    // at whole-tile refill and 2-tile claims; refill, claim
     // size and candidate ordering for the winning shape; a longer timing of
     // the best three.
     static const uint32_t kWaves[] = {4, 8, 12, 16};
     static const uint32_t kBlocks[] = {1, 2, 3, 4, 5, 6, 8};
-    static const uint32_t kCache[] = {1024, 2048, 4096};
     static const uint32_t kRefill[] = {0, 48};
     static const uint32_t kClaim[] = {1, 2, 4};
     auto time_cand = [&](const svo_config& cand, float& ms, int launches = 6) -> int {
@@ -1871,15 +1842,13 @@ int svo_tune(svo_ctx* ctx, svo_scene scene, const float* sample_rays, uint64_t n
     for (uint32_t w : kWaves)
         for (uint32_t b : kBlocks) {
             if (w * b > 32) continue;  // resident waves per CU
-            for (uint32_t c : kCache) {
-                svo_config cand = base;
-                cand.waves_per_block = w;
-                cand.blocks_per_cu = b;
-                cand.lds_cache_nodes = c;
-                cand.refill_lanes = 0;
-                cand.claim_tiles = 2;
-                cands.push_back(cand);
-            }
+            svo_config cand = base;
+            cand.waves_per_block = w;
+            cand.blocks_per_cu = b;
+            cand.lds_cache_nodes = default_config().lds_cache_nodes;
+            cand.refill_lanes = 0;
+            cand.claim_tiles = 2;
+            cands.push_back(cand);
         }
     try_all(cands, true);
     const svo_config shape1 = win;   // the first stage's winner

@@ -101,12 +101,11 @@ struct alignas(16) JobRec {
     uint32_t frame_base;      // the job's world record in the launch's frame array
     uint32_t cand_base;       // the job's first entry in the launch's candidate list
     uint32_t n_cand;
-    uint32_t lds_nodes;       // pool prefix of this job's scene held in LDS (0: none)
     uint32_t bvh_base;        // the job's hierarchy root in the launch's node array
     uint32_t n_inline;        // in-place frames, listed after the job's candidates
-    const CameraArgs* cam;    // device camera making the job's rays (rays unused), or nullptr
     uint32_t child_mask;      // bits of a node's word 1 that are its child start
-    uint32_t pad;
+    const CameraArgs* cam;    // device camera making the job's rays (rays unused), or nullptr
+    uint64_t pad;
 };
 static_assert(sizeof(JobRec) == 96, "job record must be 96 bytes");
 
@@ -209,16 +208,13 @@ constexpr size_t kStaticScratchBytes = kStaticQueueBytes + kStaticTableBytes;
 // replays, so whatever changes between replays lives in device memory.
 struct alignas(16) LaunchHdr {
     uint64_t n_rays;              // all jobs
-    const uint64_t* cache_src;    // pool whose prefix is cached in LDS (nullptr: none)
     uint64_t tile_stride;         // as TraceArgs::tile_stride, for n_rays
     uint32_t n_jobs;              // <= TraceArgs::n_jobs (the capacity)
     uint32_t n_frames;            // <= TraceArgs::n_frames
     uint32_t n_cand_total;        // <= TraceArgs::n_cand_total
-    uint32_t lds_nodes;           // <= TraceArgs::lds_nodes, even
     uint32_t n_bvh_total;         // <= TraceArgs::n_bvh_total
-    uint32_t pad0;
     double tile_inv;              // as TraceArgs::tile_inv
-    uint32_t pad[2];
+    uint32_t pad[4];
 };
 static_assert(sizeof(LaunchHdr) == 64, "launch header must be 64 bytes");
 
@@ -235,9 +231,9 @@ constexpr uint32_t kInlineTableBytes = 2048;
 // FP32 record; the entry t of the cell it hits is recomputed from this one.
 constexpr uint32_t kExactMapDoubles = 12;
 
-// In a plan launch (hdr != nullptr) n_jobs, n_frames, n_cand_total,
-// n_bvh_total and lds_nodes are capacities that size the LDS layout, and the header holds
-// the counts; n_rays, tile_stride, tile_inv and cache_src are ignored.
+// In a plan launch (hdr != nullptr) n_jobs, n_frames, n_cand_total and
+// n_bvh_total are capacities that size the LDS layout, and the header holds
+// the counts; n_rays, tile_stride and tile_inv are ignored.
 struct TraceArgs {
     const LaunchHdr* hdr;     // plan launches: counts in device memory; else nullptr
     const JobRec* jobs;       // device job table, or nullptr: the single job in job0
@@ -254,9 +250,7 @@ struct TraceArgs {
     uint32_t n_cand_total;
     uint32_t max_cand;        // largest per-job candidate count
     uint64_t n_rays;          // all jobs
-    const uint64_t* cache_src;  // pool whose prefix is cached in LDS
     uint32_t* queue;          // kQueueWords: partition counters, then finished work-groups
-    uint32_t lds_nodes;       // pool prefix cached in LDS (even)
     uint32_t stack_levels;    // traversal stack entries per lane
     uint32_t nest_levels;     // frame stack entries per lane (inline frames)
     uint32_t max_blocks;      // work-groups of this launch's size that can be resident on the device
@@ -284,8 +278,7 @@ struct TraceArgs {
     // read (each frame walked counts its root record), counts[n_rays + g]
     // frames walked, counts[2 n_rays + g] result writes (added atomically:
     // 1 when every ray is written exactly once); with trail, the index of
-    // the k-th node record read, trail[k n_rays + g] for k < trail_cap, bit
-    // 31 set when it came from the LDS copy of the pool prefix.
+    // the k-th node record read, trail[k n_rays + g] for k < trail_cap.
     uint32_t* counts;
     uint32_t* trail;
     uint32_t trail_cap;

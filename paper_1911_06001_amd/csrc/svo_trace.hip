@@ -358,8 +358,7 @@ __host__ __device__ __forceinline__ uint32_t stack_slots(const TraceArgs& a) { r
 __host__ __device__ __forceinline__ uint32_t stack_slot_bytes(const TraceArgs& a) { return a.wide ? 5u : 4u; }
 
 size_t trace_lds_bytes(const TraceArgs& a, uint32_t waves_per_block) {
-    const size_t shared = align16((size_t)a.lds_nodes * 8) + (size_t)a.n_frames * 80 +
-                          align16((size_t)a.n_cand_total * 4) + (size_t)a.n_jobs * sizeof(JobRec) +
+    const size_t shared = (size_t)a.n_frames * 80 + align16((size_t)a.n_cand_total * 4) + (size_t)a.n_jobs * sizeof(JobRec) +
                           (size_t)a.n_bvh_total * sizeof(BvhNode) + (a.jobs ? 0 : kHotLdsBytes) +
                           (a.has_cam0 ? sizeof(CameraArgs) : 0);
     const size_t per_wave = (size_t)cand_slots(a) * 256 + align16((size_t)stack_slots(a) * 64 * stack_slot_bytes(a)) +
@@ -391,8 +390,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     typename std::conditional<kInline, TraceArgsInline, TraceArgs>::type a) {
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* p = smem;
-    uint64_t* lds_nodes = reinterpret_cast<uint64_t*>(p);
-    p += align16((size_t)a.lds_nodes * 8);
     FrameRec* lds_frames = reinterpret_cast<FrameRec*>(p);
     p += (size_t)a.n_frames * 64;
     float4* lds_sph = reinterpret_cast<float4*>(p);
@@ -430,9 +427,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     // launch-wide counts: the arguments, or a plan's header (capacities
     // above bound them, so every LDS copy below stays in its region)
     uint64_t n_rays = a.n_rays;
-    uint32_t n_jobs = a.n_jobs, n_frames = a.n_frames, n_cand_total = a.n_cand_total, fill_nodes = a.lds_nodes;
+    uint32_t n_jobs = a.n_jobs, n_frames = a.n_frames, n_cand_total = a.n_cand_total;
     uint32_t n_bvh = a.n_bvh_total;
-    const uint64_t* cache_src = a.cache_src;
     uint32_t tstride = (uint32_t)a.tile_stride;
     double tile_inv = a.tile_inv;
     if (a.hdr) {
@@ -443,10 +439,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
         n_jobs = min(h.n_jobs, a.n_jobs);
         n_frames = min(h.n_frames, a.n_frames);
         n_cand_total = min(h.n_cand_total, a.n_cand_total);
-        fill_nodes = min(h.lds_nodes, a.lds_nodes);
         n_bvh = min(h.n_bvh_total, a.n_bvh_total);
-        cache_src = h.cache_src;
-        if (!cache_src) fill_nodes = 0;
         if (n_jobs == 0) n_rays = 0;
     }
     // work-groups beyond what this launch's rays need (a plan's grid is
@@ -456,13 +449,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     const uint32_t n_active = min(gridDim.x, (n_tiles + wpb - 1u) / wpb);
     const bool active = blockIdx.x < n_active;
     if (!active) {
-        fill_nodes = 0;
         n_frames = 0;
         n_cand_total = 0;
         n_bvh = 0;
         n_jobs = 0;
     }
-    for (uint32_t i = threadIdx.x; i < fill_nodes; i += blockDim.x) lds_nodes[i] = cache_src[i];
     // the frame table: in the arguments (small one-job launches) or in
     // device memory
     const FrameRec* src_frames = a.frames;
@@ -558,7 +549,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     // partition, and the counters count on from the fixed ones.  Such a launch
     // is over in the time of a tile or two, and a few atomic round trips (about
     // 0.8 us each) to claim a tile and to find the rest claimed are a good part
-    // of that (256x256 rays: 30.8 us fixed).  A larger one gains nothing by it,
+    // of that (256x256 rays: 26.5 us fixed, 29.7 by the counters; 100 rays 37.5
+    // and 40.5).  A larger one gains nothing by it (1080p: 157.5 either way),
     // and where another stream's launch still holds part of the device, its
     // last work-groups start late: tiles kept for them would wait.
     const bool fixed = 2u * n_active <= a.max_blocks;
@@ -594,7 +586,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
     // read from the arguments, they would share one wide scalar load with
     // fields the loop never uses, and be kept or spilled with them
     const uint64_t* nodes = kSingle ? uniform_ptr(lds_jobs[0].nodes) : nullptr;
-    uint32_t n_lds = kSingle ? min(uniform_u32(lds_jobs[0].lds_nodes), fill_nodes) : 0u;
     uint32_t fbase = kSingle ? uniform_u32(lds_jobs[0].frame_base) : 0u;
     uint32_t cbase = kSingle ? uniform_u32(lds_jobs[0].cand_base) : 0u;
     uint32_t ncand = kSingle ? uniform_u32(lds_jobs[0].n_cand) : 0u;
@@ -936,7 +927,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
                         const JobRec& J = lds_jobs[job];
                         ri = (uint32_t)(gidx - J.ray_begin);
                         nodes = J.nodes;
-                        n_lds = min(J.lds_nodes, fill_nodes);
                         if constexpr (kWide) cmask = J.child_mask;
                         fbase = J.frame_base;
                         cbase = J.cand_base;
@@ -1099,16 +1089,17 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 
                 }
                 opaque(full);
                 if (full != 0u) {
-                    // descend: the child's node word, from the LDS copy of the
-                    // pool's prefix or from the pool (separate LDS and global
-                    // reads: a select between the two would become one generic
-                    // load waiting on both counters)
+                    // descend: the child's node word.  (A copy of the pool's
+                    // first nodes in LDS took seven more instructions per
+                    // turn to choose between the two and to fill, and the
+                    // vector cache holds those nodes as well: 160.7 us with it
+                    // and 157.5 us without on the 1080p terrain under a moving
+                    // camera, instances 298 and 282 us, 100 rays 38.7 and 37.2.)
                     evd = (kWide ? pchild : pw >> 8) + __popc(__builtin_amdgcn_ubfe(pw, 0, oct));
-                    uint64_t w = lds_nodes[evd < n_lds ? evd : 0u];
-                    if (evd >= n_lds) w = kWide ? gld(nodes, evd) : gld_at32(nodes, evd * 8u);
+                    const uint64_t w = kWide ? gld(nodes, evd) : gld_at32(nodes, evd * 8u);
                     if constexpr (kCount) {
                         if (a.trail && c_trail < a.trail_cap)
-                            gst(a.trail, (uint64_t)c_trail * n_rays + gray, evd | ((evd < n_lds) ? 0x80000000u : 0u));
+                            gst(a.trail, (uint64_t)c_trail * n_rays + gray, evd);
                         ++c_trail;
                         ++c_nodes;
                     }
