@@ -367,14 +367,15 @@ size_t trace_lds_bytes(const TraceArgs& a, uint32_t waves_per_block) {
 }
 
 // kSorted: every job's candidates are tested one by one (at most 16 of
-// them); otherwise through the per-frame box hierarchy.  A launch
-// uses one of the two, and each instantiation carries only its own path,
-// which keeps the sorted one at fewer registers.  The sorted one is compiled
-// for 6 resident waves per SIMD (80 VGPRs): the few values that then go to
-// scratch are per-ray state outside the walk loop, and the extra waves hide
-// more of the node-load latency.  The hierarchy one keeps its natural
-// count (97 VGPRs single-job, 108 batched; 103 and 112 wide): forcing it
-// lower spills inside its candidate search.
+// them); otherwise through the per-frame box hierarchy.  A launch uses one of
+// the two, and each instantiation carries only its own path.  All but one are
+// compiled for 6 resident waves per SIMD (80 VGPRs): the few values that then
+// go to scratch are per-ray state outside the walk loop, and the extra waves
+// hide more of the node-load latency.  (Hierarchy at its natural 106 VGPRs, 4
+// waves: instances 288 us, their AO rays 462; at 5 waves 273 and 435; at 6
+// waves 270 and 420.  One-by-one at 7 waves: 1080p terrain 139 us, at 6 waves
+// 128.)  The wide hierarchy one is compiled for 5 (96 VGPRs): 4096^3 terrain
+// 1,586 us at 4 waves, 1,564 at 5, 1,647 at 6, where it spills more.
 // kSingle: a one-job launch (the job in the arguments), whose pool, cache
 // size and table offsets are then launch-wide values (scalar registers)
 // rather than per-lane ones.
@@ -386,7 +387,7 @@ size_t trace_lds_bytes(const TraceArgs& a, uint32_t waves_per_block) {
 // kCount: the counting build (TraceArgs::counts and trail), for tests and
 // measurement only.
 template <bool kSorted, bool kSingle, bool kInline, bool kWide, bool kCount = false>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ? 6 : 1, 8))) void trace_kernel(
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted || !kWide ? 6 : 5, 8))) void trace_kernel(
     typename std::conditional<kInline, TraceArgsInline, TraceArgs>::type a) {
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* p = smem;
