@@ -30,47 +30,54 @@ __device__ __forceinline__ uint32_t mix32(uint32_t x) {
 
 __device__ __forceinline__ float unit24(uint32_t h) { return (float)(h >> 8) * 0x1p-24f; }
 
+// floor(a / b) with inv_b = 1 / b (FP64): a + 1/2 keeps the quotient at least
+// 1 / (2 b) away from every whole number, more than the roundings of inv_b and
+// the product can move it (2^-52 a / b) while a < 2^51.  A multiply where the
+// integer division takes about 25 instructions (32 bits; 64 bits: over 100).
+__device__ __forceinline__ uint32_t div_exact(double a, double inv_b) { return (uint32_t)((a + 0.5) * inv_b); }
+
 // Pixel (x, y) of the pix-th pixel in ray order.
-__device__ __forceinline__ void pixel_of(uint32_t pix, uint32_t W, uint32_t H, uint32_t tiled, uint32_t& x,
+__device__ __forceinline__ void pixel_of(uint32_t pix, uint32_t W, uint32_t H, double inv_w, bool tiled, uint32_t& x,
                                          uint32_t& y) {
     if (tiled) {
-        const uint32_t ty = pix / (8u * W);
+        const uint32_t ty = div_exact((double)pix, 0.125 * inv_w);
         uint32_t rem = pix - ty * 8u * W;
         const uint32_t h = min(8u, H - 8u * ty);
-        const uint32_t tx = rem / (8u * h);
+        // a whole tile shifts; only an edge's partial one divides
+        uint32_t tx = rem >> 6;
+        if (h != 8u) tx = rem / (8u * h);
         rem -= tx * 8u * h;
         const uint32_t w = min(8u, W - 8u * tx);
-        y = 8u * ty + rem / w;
-        x = 8u * tx + rem % w;
+        uint32_t row = rem >> 3;
+        if (w != 8u) row = rem / w;
+        y = 8u * ty + row;
+        x = 8u * tx + (rem - row * w);
     } else {
-        y = pix / W;
-        x = pix % W;
+        y = div_exact((double)pix, inv_w);
+        x = pix - y * W;
     }
 }
 
 // Ray i of camera c: origin at the eye, tmin 0, tmax +inf, direction through
 // the pixel sample, normalised.  With whole 8x8 tiles and one sample per
-// pixel (c.full_tiles) the ray's 64-ray tile is its pixel tile, found with
-// one FP64 multiply instead of integer divisions.
+// pixel (kCamFullTiles) the ray's 64-ray tile is its pixel tile.
 __device__ __forceinline__ void camera_ray(const CameraArgs& c, uint32_t i, float4& r0, float4& r1) {
     uint32_t x, y, pix, smp;
-    if (c.full_tiles) {
+    if (c.flags & kCamFullTiles) {
         const uint32_t T = i >> 6, k = i & 63u;
-        uint32_t ty = (uint32_t)((double)T * c.inv_tiles_x);
-        if (ty * c.tiles_x > T) --ty;
-        else if ((ty + 1u) * c.tiles_x <= T) ++ty;
-        const uint32_t tx = T - ty * c.tiles_x;
+        const uint32_t ty = div_exact((double)T, 8.0 * c.inv_width);
+        const uint32_t tx = T - ty * (c.width >> 3);
         x = 8u * tx + (k & 7u);
         y = 8u * ty + (k >> 3);
         pix = i;
         smp = 0;
     } else {
-        pix = i / c.samples;
+        pix = div_exact((double)i, c.inv_samples);
         smp = i - pix * c.samples;
-        pixel_of(pix, c.width, c.height, c.tiled, x, y);
+        pixel_of(pix, c.width, c.height, c.inv_width, (c.flags & kCamTiled) != 0u, x, y);
     }
     float fx = 0.5f, fy = 0.5f;
-    if (c.jitter) {
+    if (c.flags & kCamJitter) {
         const uint32_t h = mix32(c.seed ^ mix32(pix * 0x9e3779b9u + smp));
         fx = unit24(mix32(h ^ 0x68e31da4u));
         fy = unit24(mix32(h ^ 0xb5297a4du));

@@ -1132,11 +1132,10 @@ int camera_args(const svo_camera* cam, svo::CameraArgs& c) {
     c.height = cam->height;
     c.samples = cam->samples;
     c.seed = cam->seed;
-    c.jitter = cam->jitter ? 1u : 0u;
-    c.tiled = cam->tiled ? 1u : 0u;
-    c.full_tiles = (c.tiled && c.samples == 1 && c.width % 8 == 0 && c.height % 8 == 0) ? 1u : 0u;
-    c.tiles_x = (c.width + 7) / 8;
-    c.inv_tiles_x = 1.0 / (double)c.tiles_x;
+    c.flags = (cam->jitter ? svo::kCamJitter : 0u) | (cam->tiled ? svo::kCamTiled : 0u);
+    if (cam->tiled && c.samples == 1 && c.width % 8 == 0 && c.height % 8 == 0) c.flags |= svo::kCamFullTiles;
+    c.inv_width = 1.0 / (double)c.width;
+    c.inv_samples = 1.0 / (double)c.samples;
     return SVO_OK;
 }
 
@@ -1942,6 +1941,8 @@ int svo_shade(svo_ctx* ctx, svo_scene scene, const uint32_t* prim_id, const uint
     a.k = k;
     a.ambient = ambient_permille;
     a.background = background_rgba;
+    a.inv_width = 1.0 / (double)width;
+    a.inv_total = 1.0 / (1000.0 * (k ? k : 1u) * samples);
     a.out = out_rgba;
     const hipError_t e = svo::launch_shade(a, (hipStream_t)stream);
     if (e != hipSuccess) return fail(SVO_EDEVICE, "shade launch failed: %s", hipGetErrorString(e));
@@ -1974,6 +1975,7 @@ int svo_generate_ao_rays(svo_ctx* ctx, const float* rays, const float* t, const 
     a.normal = normal;
     a.n = n;
     a.k = k;
+    a.inv_k = 1.0 / (double)k;
     a.seed = seed;
     a.radius = radius;
     a.offset = offset;

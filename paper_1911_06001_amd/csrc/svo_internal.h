@@ -80,13 +80,14 @@ struct alignas(16) CameraArgs {
     float eye[3], fwd[3], right[3], up[3];
     float tan_half_fov, aspect;
     uint32_t width, height, samples, seed;
-    uint32_t jitter;      // 0: pixel centres
-    uint32_t tiled;       // 1: 8x8 tile order
-    uint32_t full_tiles;  // tiled, one sample, width and height multiples of 8
-    uint32_t tiles_x;     // width / 8
-    double inv_tiles_x;   // 1 / tiles_x
+    uint32_t flags;       // kCam*
+    uint32_t pad;
+    double inv_width, inv_samples;
 };
 static_assert(sizeof(CameraArgs) == 96, "camera record must be 96 bytes");
+constexpr uint32_t kCamJitter = 1;      // else pixel centres
+constexpr uint32_t kCamTiled = 2;       // 8x8 tile order
+constexpr uint32_t kCamFullTiles = 4;   // tiled, one sample, width and height multiples of 8
 
 // One job of a launch: a ray range traced against one scene under one set
 // of transforms (96 bytes, held in LDS).
@@ -308,6 +309,7 @@ struct AoArgs {
     uint64_t n;
     uint32_t k;               // AO rays per primary ray
     uint32_t seed;
+    double inv_k;
     float radius;             // AO ray tmax
     float offset;             // origin lift along the normal, relative to max(1, |p|inf)
     float4* out;              // n * k rays
@@ -324,6 +326,8 @@ struct ShadeArgs {
     uint32_t width, height, samples, tiled, k;
     uint32_t ambient;         // per mille of the colour kept when every AO ray is blocked
     uint32_t background;      // RGBA8 of a miss
+    double inv_width;
+    double inv_total;         // 1 / (1000 max(k, 1) samples)
     uint32_t* out;            // width * height, row-major
 };
 
