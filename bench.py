@@ -143,7 +143,7 @@ def replay_ceiling(ctx, handle, sc, fwd, rays, kc, n_cu, reps=5, max_cap=512):
     out = torch.empty(6 * n, dtype=torch.int32, device=rays.device)
     blocks, threads = n_cu * kc["blocks_per_cu"], 64 * kc["waves_per_block"]
     sink = torch.empty(blocks * threads, dtype=torch.int64, device=rays.device)
-    n_lds = int(min(kc["lds_cache_nodes"], 16384, sc.nodes.shape[0]))
+    n_lds = 0   # the trace reads every node through the caches
     t_rep = ceiling._time(lambda: ceiling.replay(nodes, n_lds, trail, counts, rays, out, blocks, threads, sink,
                                                  stream), reps)
     hits = ctx.trace(handle, rays)

@@ -127,10 +127,11 @@ typedef struct {
     uint32_t refill_lanes;      /* 0 or 64: a wave takes 64-ray tiles; 1..63: claim new rays once that many lanes are idle */
     uint32_t step_limit;        /* cell advances plus candidate selections per ray before SVO_STEP_LIMIT */
     uint32_t claim_tiles;       /* 64-ray tiles a wave takes from the work queue at once (0: 2; at most 64) */
-    uint32_t sorted_candidates; /* 0: 16; 1..64: a job with at most this many candidate frames orders them by
-                                   entry with a per-lane sorted table (the depth sort of Sec. 4.2), one with more
-                                   through the box hierarchy over their world boxes (a scene whose table travels
-                                   in the kernel arguments always takes the sorted table) */
+    uint32_t sorted_candidates; /* 0: 16; 1..64: a job with at most this many candidate frames tests each ray
+                                   against them one by one, one with more through the box hierarchy over their
+                                   world boxes; both trace them in order of entry (the depth sort of Sec. 4.2).
+                                   A scene whose table travels in the kernel arguments is always tested one by
+                                   one; a launch of several jobs, or a plan, goes by the context's value */
     uint32_t tile_order;        /* 0: slow tiles first, 1: the plain claim order.  With 0, a one-job trace with
                                    whole-tile claims (refill_lanes 0 or 64; not the hit buffer) lists the 64-ray
                                    tiles whose slowest ray took the most walk steps (about the slowest 12 %) in
@@ -428,7 +429,7 @@ int svo_set_config(svo_ctx* ctx, const svo_config* cfg);
 /* Autotuner.  Times candidate kernel configurations on n device sample rays
    against `scene` under its current transforms, in two stages: the launch
    shape (waves per work-group, work-groups per CU), then lane refill, tiles per work-queue claim and the candidate ordering
-   (sorted table or hierarchy) for the fastest shape, then five times longer timings of that winner, the first
+   (one by one or hierarchy) for the fastest shape, then five times longer timings of that winner, the first
    stage's winner and the next two shapes.  Infrastructure: no passage of the paper defines it.  Keeps
    the fastest for that scene -- later svo_trace_rays calls on it use it, and
    a batch uses it when that scene holds most of the batch's rays -- and

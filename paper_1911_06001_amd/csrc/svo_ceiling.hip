@@ -106,9 +106,9 @@ __global__ __launch_bounds__(1024) void stream_kernel(const v4u* __restrict__ bu
 // each lane takes one ray (64 consecutive rays per wave, waves striding
 // over the 64-ray tiles), reads the ray (32 bytes), then, in order, the
 // node words its trace read -- trail[k n + g] for k below the ray's pool
-// reads (counts[g] - counts[n + g]) and cap, from the LDS copy of the pool
-// prefix when bit 31 is set (every work-group fills it first, as the trace
-// does) -- each load's address waiting on the word before it (the walk
+// reads (counts[g] - counts[n + g]) and cap, from an LDS copy of the pool's
+// first n_lds nodes when bit 31 is set (the trace reads every node through the
+// caches and sets it on none) -- each load's address waiting on the word before it (the walk
 // decides its next step from the node it just read; dep_mask = 0 keeps the
 // addresses unchanged), and writes 24 bytes of result.
 __global__ __launch_bounds__(1024) void replay_kernel(const uint64_t* __restrict__ nodes, uint32_t n_nodes, uint32_t n_lds,

@@ -412,7 +412,7 @@ int check_config(const svo_config& c) {
     return SVO_OK;
 }
 
-// Candidates up to which a job takes the per-lane sorted entry table.
+// Candidates up to which a job tests them one by one.
 uint32_t sort_limit(const svo_config& c) {
     return c.sorted_candidates ? c.sorted_candidates : svo::kMaxSortedCand;
 }
@@ -1862,9 +1862,9 @@ int svo_tune(svo_ctx* ctx, svo_scene scene, const float* sample_rays, uint64_t n
                 cand.claim_tiles = y;
                 cands.push_back(cand);
             }
-        // the other candidate ordering: the box hierarchy for a scene that
-        // takes the sorted table, the sorted table (up to 64) for one that
-        // takes the hierarchy
+        // the other candidate path: the box hierarchy for a scene whose
+        // candidates are tested one by one, one by one (up to 64) for one
+        // that takes the hierarchy
         if (S->n_cand > 1 && S->n_cand <= 64) {
             svo_config other = shape;
             other.sorted_candidates = S->n_cand <= sort_limit(shape) ? S->n_cand - 1 : 64u;

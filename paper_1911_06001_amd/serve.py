@@ -270,7 +270,7 @@ class Server:
         """One plan per in-flight slot, its launch captured into a graph."""
         t = self.torch
         handles = [e.handle for e in self.scenes.values()]
-        # the scene with the most pool nodes first: its prefix sizes the LDS cache
+        # the scene with the most pool nodes first: a plan takes its tuned configuration
         handles.sort(key=lambda h: -self.ctx.scene_stats(h).device_bytes)
         for _ in range(self.inflight_steps):
             plan = self.ctx.plan(handles, max_jobs=self.max_jobs, max_frames=self.max_frames)
