@@ -1094,6 +1094,10 @@ void fill_common(const svo_config& c, svo::TraceArgs& a) {
     a.step_limit = c.step_limit;
 }
 
+// Whether a launch of n rays (32 B each, 24 B of hit) into S reads its rays
+// past the caches.
+bool stream_rays(const Scene& S, uint64_t n) { return S.n_nodes * 8ull + n * 56ull > svo::kStreamBytes; }
+
 // Signature of a ray set, to tell whether a launch traces the rays of the
 // previous one on its queue (FNV-1a over scene, ray pointer, count and
 // camera record).
@@ -1334,6 +1338,7 @@ int trace_rays(svo_ctx* ctx, svo_scene scene, const float* rays, uint64_t n, uin
     a.nest_levels = S->nest_levels;
     a.sort_cand = sorted ? 1u : 0u;
     a.wide = wide_pool(*S) ? 1u : 0u;
+    a.stream_rays = stream_rays(*S, n) ? 1u : 0u;
     fill_common(cfg, a);
     a.reuse = reuse ? 1u : 0u;
     a.retraced = retraced;
@@ -1519,6 +1524,7 @@ int trace_batch(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, void* stream
             a.inline_off_cand = (uint32_t)cand_offset(S.n_frames);
             a.inline_off_sph = (uint32_t)sphere_offset(S.n_frames, S.n_slots);
             a.inline_off_x = (uint32_t)xmap_offset(S.n_frames, S.n_slots);
+            a.stream_rays = stream_rays(S, P.total) ? 1u : 0u;
             const unsigned char* tab = Q.table.empty() ? S.h_stage[S.cur] : Q.table.data();
             if (use_static) HIP_TRY(svo::launch_zero_words(queue, svo::kQueueWords, st));
             return launch(ctx, cfg, a, st, tab, bvh_offset(S.n_frames, S.n_slots));

@@ -235,6 +235,16 @@ constexpr uint32_t kExactMapDoubles = 12;
 // In a plan launch (hdr != nullptr) n_jobs, n_frames, n_cand_total and
 // n_bvh_total are capacities that size the LDS layout, and the header holds
 // the counts; n_rays, tile_stride and tile_inv are ignored.
+// A launch whose pool, rays and hits together are larger than this reads its
+// rays with the streaming hint: they would only push nodes out of the L2s and
+// the 256 MB last-level cache, and are gone from there before they are traced
+// again.  Without / with the hint, new cameras: terrain (18 MB pool) at
+// 2,822,400 rays (176 MB) 180 / 184 us, at 3,686,400 (225 MB) 225 / 217; at
+// 8,294,400 376 / 368; 4096^3 terrain (1.18 GB pool) at 921,600 rays 365 / 353,
+// at 8,294,400 1,561 / 1,491; four AO rays of each of 2,073,600 instance hits
+// 406 / 389; terrain at 2,073,600 rays (134 MB) 154 / 161.
+constexpr uint64_t kStreamBytes = (uint64_t)192 << 20;
+
 struct TraceArgs {
     const LaunchHdr* hdr;     // plan launches: counts in device memory; else nullptr
     const JobRec* jobs;       // device job table, or nullptr: the single job in job0
@@ -259,6 +269,7 @@ struct TraceArgs {
     uint32_t sort_cand;       // 1: candidates tested one by one, 0: through the hierarchy
     uint32_t refill;          // a wave claims new rays once this many lanes are idle (1..64)
     uint32_t claim;           // rays a wave takes from a partition counter at once (a multiple of 64)
+    uint32_t stream_rays;     // one job, 1: its rays are read past the caches (see kStreamBytes)
     uint32_t reuse;           // 1: the outputs hold the previous trace of these rays (hit buffer)
     unsigned long long* retraced;  // reuse: rays traced again are added here (nullable)
     uint64_t tile_stride;     // claim i covers tile (i * tile_stride) mod tiles (coprime: a permutation)

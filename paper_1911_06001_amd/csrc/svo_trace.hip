@@ -350,6 +350,18 @@ __device__ __forceinline__ T gld(const T* p, uint64_t i) {
 __device__ __forceinline__ uint64_t gld_at32(const uint64_t* p, uint32_t byte) {
     return *(const __attribute__((address_space(1))) uint64_t*)((const __attribute__((address_space(1))) char*)p + byte);
 }
+// Loads and stores with the streaming hint, for what this launch touches once.
+// Hits always go out with it, so that they push fewer nodes out of the L2s:
+// 1080p terrain under moving cameras 158 -> 150 us, instances 268 -> 260, their
+// AO rays 428 -> 406 (a following pass over the hits is no slower).
+template <typename T>
+__device__ __forceinline__ T gld_once(const T* p, uint64_t i) {
+    return __builtin_nontemporal_load((const __attribute__((address_space(1))) T*)p + i);
+}
+template <typename T>
+__device__ __forceinline__ void gst_once(T* p, uint64_t i, T v) {
+    __builtin_nontemporal_store(v, (__attribute__((address_space(1))) T*)p + i);
+}
 template <typename T>
 __device__ __forceinline__ void gst(T* p, uint64_t i, T v) {
     ((__attribute__((address_space(1))) T*)p)[i] = v;
@@ -789,13 +801,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
             gst(a.counts, n_rays + gray, c_frames);
             atomicAdd(a.counts + 2 * n_rays + gray, 1u);
         }
-        gst(J.out_id, ri, best_id);
-        if (J.out_inst) gst(J.out_inst, ri, best_inst);
-        gst(J.out_t, ri, best_t);
+        gst_once(J.out_id, ri, best_id);
+        if (J.out_inst) gst_once(J.out_inst, ri, best_inst);
+        gst_once(J.out_t, ri, best_t);
         if (J.out_n) {
-            gst(J.out_n, 3 * (uint64_t)ri, nx);
-            gst(J.out_n, 3 * (uint64_t)ri + 1, ny);
-            gst(J.out_n, 3 * (uint64_t)ri + 2, nz);
+            gst_once(J.out_n, 3 * (uint64_t)ri, nx);
+            gst_once(J.out_n, 3 * (uint64_t)ri + 1, ny);
+            gst_once(J.out_n, 3 * (uint64_t)ri + 2, nz);
         }
         mode = M_DONE;
     };
@@ -977,8 +989,18 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
                     }
                     if (!made) {
                         const v4f* rp = reinterpret_cast<const v4f*>(rays);
-                        const v4f r0 = gld(rp, 2 * (uint64_t)ri);
-                        const v4f r1 = gld(rp, 2 * (uint64_t)ri + 1);
+                        v4f r0, r1;
+                        if (kSingle && a.stream_rays) {
+                            // between marks that keep the compiler from merging
+                            // the two branches' loads, which would drop the hint
+                            asm volatile("");
+                            r0 = gld_once(rp, 2 * (uint64_t)ri);
+                            r1 = gld_once(rp, 2 * (uint64_t)ri + 1);
+                            asm volatile("");
+                        } else {
+                            r0 = gld(rp, 2 * (uint64_t)ri);
+                            r1 = gld(rp, 2 * (uint64_t)ri + 1);
+                        }
                         r = Ray{r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
                     }
                     best_t = INFINITY;
