@@ -47,16 +47,17 @@
 // regular order skips them; results never depend on the order.
 //
 // What bounds it: instruction issue while tiles are left (56 % of the VALU
-// rate over a whole 1080p terrain launch, 82 % over a 4K launch on the 4096^3
-// terrain), then the longest chains of dependent walk steps; memory only
+// rate over a whole 1080p terrain launch under a moving camera, 83 % over a 4K
+// launch on the 4096^3 terrain), then the longest chains of dependent walk steps; memory only
 // through their latency (the 1080p terrain moves 116 MB of rays and hits in
-// 129 us).  So the walk is laid out for few instructions per step: one turn of
+// 126 us).  So the walk is laid out for few instructions per step: one turn of
 // its loop advances and then descends (14.4 turns per 64-ray tile where a turn
 // that did either took 19.5), node words come ready to push (absolute child
 // starts, encoded at upload), and the loop keeps no lane masks.  Together with
-// the queue, the candidate listing and the register budgets below: 1080p
-// terrain under moving cameras 215 -> 153 us, the same rays again 174 -> 129,
-// 64 instances 400 -> 270, 4K on the 4096^3 terrain 2,185 -> 1,564.
+// the queue, the candidate listing, the register budgets and the streaming
+// hints below: 1080p terrain under moving cameras 220 -> 149 us, the same rays
+// again 174 -> 126, 64 instances 375 -> 242, 4K on the 4096^3 terrain 2,176 ->
+// 1,478.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
