@@ -1321,8 +1321,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
                 if (__uint_as_float(near & ~kCandIndexMask) > fmaxf(tl, 0.f)) {
                     n_lst = 0;   // the nearest lies beyond the best hit, and so do the others
                     if (c_next >= ncand) finish();
+                    else --steps;   // (nothing was selected)
                 } else if (start_frame(lds_cand[cbase + (near & kCandIndexMask)])) {
                     mode = M_WALK;
+                } else {
+                    // a frame that the walk's own entry test misses, which is
+                    // narrower than the list's, is no selection
+                    --steps;
                 }
             }
         }

@@ -1,0 +1,80 @@
+"""Which candidate frames a ray walks, and in what order: what it counts
+against the step limit, the frames a counted trace reports and the rays a
+hit-buffer launch traces again, in launches that test the candidates one by
+one and through the box hierarchy (needs the GPU)."""
+import numpy as np
+import pytest
+
+from svogen import scenes
+
+pytestmark = pytest.mark.gpu
+
+CELL = 8.0      # edge of a part's cell: level 2 of a 32^3 world
+LIMITED = -2    # the id of a ray that the step limit ended
+
+
+def parts(n, places):
+    """n parts, part s with its cell moved to places[s]: a slab over the
+    cell's half at low z.  The world around them is one voxel."""
+    cells = [(2, (s % 4, s // 4 % 4, s // 16)) for s in range(n)]
+    occ = np.zeros((32, 32, 32), bool)
+    for _, (x, y, z) in cells:
+        occ[8 * x:8 * x + 8, 8 * y:8 * y + 8, 8 * z:8 * z + 4] = True
+    occ[31, 31, 31] = True
+    fwd = np.zeros((n, 3, 4), np.float32)
+    fwd[:, [0, 1, 2], [0, 1, 2]] = 1.0
+    fwd[:, :, 3] = np.asarray(places, np.float64) - CELL * np.array([c for _, c in cells])
+    return scenes.from_occupancy(occ, cells, fwd.reshape(n, 12), name="parts")
+
+
+def rays(origins, direction):
+    d = np.asarray(direction, np.float64)
+    r = np.zeros((len(origins), 8), np.float32)
+    r[:, 0:3], r[:, 4:7], r[:, 7] = origins, d / np.linalg.norm(d), np.inf
+    return r
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1911_06001_amd import svo
+    with svo.Context(0) as c:
+        yield c
+
+
+@pytest.fixture(params=[64, 1], ids=["one by one", "hierarchy"])
+def limit(ctx, request):
+    ctx.set_config(sorted_candidates=request.param)
+    yield request.param
+    ctx.set_config(sorted_candidates=0, step_limit=1 << 20)
+
+
+def upload(ctx, sc):
+    h = ctx.upload_scene(sc)
+    ctx.set_transforms(h, sc.xform(0))
+    st = ctx.scene_stats(h)
+    assert st.n_candidates == sc.n_slots > 10    # (a table of up to 10 slots is always tested one by one)
+    return h
+
+
+def passed_by(n):
+    """n parts in a row towards +y and +z, and rays across the row's x whose
+    direction has no x: they miss the world, pass each cell's edge by up to
+    0.4 and meet each cell's bounding sphere."""
+    at = [(44.0, 40.0 + 10 * s, 40.0 + 10 * s) for s in range(n)]
+    k = np.arange(64)
+    return at, rays(np.stack([46.0 + k / 16.0, 28.1 + k / 200.0, np.full(64, 20.0)], 1), (0, 1, 1))
+
+
+def test_parts_a_ray_passes_by_count_no_step(ctx, limit):
+    """A selection that starts no walk is none: a ray that misses the world
+    and every part needs one step, whatever its first tests met."""
+    import torch
+    at, r = passed_by(12)
+    h = upload(ctx, parts(12, at))
+    ctx.set_config(step_limit=1)
+    out = ctx.trace(h, torch.from_numpy(r).cuda())
+    torch.cuda.synchronize()
+    assert bool((out.id == -1).all()), int((out.id == LIMITED).sum())
+    ctx.free_scene(h)
