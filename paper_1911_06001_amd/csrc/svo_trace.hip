@@ -312,16 +312,22 @@ __device__ __forceinline__ bool box_hit(const BvhNode& B, const BoxRay& b, float
 __device__ __forceinline__ uint32_t bvh_end(const BvhNode& root) { return (root.b & kBvhLeaf) ? 1u : root.a; }
 
 // Whether the ray may enter frame F's root cell by tlimit, and then a t0 no
-// later than it does (to rounding): the root clip of frame_setup with the
-// hardware reciprocal, widened by more than the two can differ, so that no
-// frame that a walk would enter is ruled out.
+// later than it does: the root clip of frame_setup with the hardware
+// reciprocal, each plane's t widened by more than the two can differ, so that
+// no frame that a walk would enter is ruled out.  Plane by plane, because a
+// direction along an axis has planes at 2^21 times the others' t, beside
+// whose rounding every box on the ray's line would pass.
 __device__ __forceinline__ bool may_enter(const FrameRec& F, const Ray& r, float tlimit, float& t0) {
+    constexpr float kSlack = 0x1p-19f;
     FrameRay fr;
     frame_setup<false>(F, r, tlimit, fr, t0);
     const float N = (float)(1u << fr.K);
-    const float tx = min3f(fmaf(N, fr.ix, fr.bx), fmaf(N, fr.iy, fr.by), fmaf(N, fr.iz, fr.bz));
-    const float slack = fmaxf(max3f(fabsf(fr.bx), fabsf(fr.by), fabsf(fr.bz)), fabsf(t0)) * 0x1p-19f;
-    return t0 - slack <= fminf(tx, tlimit);
+    auto exit_by = [&](float i, float b) {
+        const float t = fmaf(N, i, b);
+        return fmaf(fabsf(t) + fabsf(b), kSlack, t);
+    };
+    t0 = fmaf(-fabsf(t0), kSlack, t0);   // (grows with t0: the last plane entered stays the last)
+    return t0 < INFINITY && t0 <= fminf(min3f(exit_by(fr.ix, fr.bx), exit_by(fr.iy, fr.by), exit_by(fr.iz, fr.bz)), tlimit);
 }
 
 // Whether any active lane's v holds (wave-uniform).

@@ -78,3 +78,22 @@ def test_parts_a_ray_passes_by_count_no_step(ctx, limit):
     torch.cuda.synchronize()
     assert bool((out.id == -1).all()), int((out.id == LIMITED).sum())
     ctx.free_scene(h)
+
+
+def test_parts_a_ray_passes_by_keep_its_last_hit(ctx, limit):
+    """The hit buffer traces a ray again only if a part may reach it; a
+    direction along a coordinate plane widens no entry test but that plane's
+    own."""
+    import torch
+    at, r = passed_by(12)
+    sc = parts(12, at)
+    h = upload(ctx, sc)
+    dev = torch.from_numpy(r).cuda()
+    out = ctx.trace(h, dev)
+    ctx.set_transforms(h, sc.xform(0))
+    again = torch.zeros(1, dtype=torch.int64, device="cuda")
+    ctx.trace_reuse(h, dev, out, retraced=again)
+    torch.cuda.synchronize()
+    assert int(again) == 0
+    assert bool((out.id == -1).all())
+    ctx.free_scene(h)
