@@ -52,10 +52,8 @@ constexpr uint32_t kMaxInlineNest = 4;
 // Candidates are tested one by one up to this many; beyond, they are found
 // through a bounding-box hierarchy.
 constexpr uint32_t kMaxSortedCand = 16;
-// A ray's list of candidates to walk holds this many at a time; an entry's
-// low bits are the candidate's place in its job's list (at most 1022).
+// A ray's list of candidates to walk holds this many at a time.
 constexpr uint32_t kCandList = 8;
-constexpr uint32_t kCandIndexMask = 0x7FFu;
 
 // One node of a frame table's hierarchy over its candidate frames, in
 // preorder: the world-space box of the moved root cells below it (widened

@@ -377,7 +377,9 @@ __device__ __forceinline__ void gst(T* p, uint64_t i, T v) {
 }  // namespace
 
 // Per-lane candidate list in LDS: up to kCandList entries (most rays have
-// none to three; one with more lists the rest when these are done).
+// none to three; one with more lists the rest when these are done), an entry t
+// and the candidate's place in the job's list (16 bits) each.
+constexpr uint32_t kCandEntryBytes = 64 * (4 + 2);   // of a wave
 __host__ __device__ __forceinline__ uint32_t cand_slots(const TraceArgs& a) {
     return a.max_cand < kCandList ? a.max_cand : kCandList;
 }
@@ -392,7 +394,7 @@ size_t trace_lds_bytes(const TraceArgs& a, uint32_t waves_per_block) {
     const size_t shared = (size_t)a.n_frames * 80 + align16((size_t)a.n_cand_total * 4) + (size_t)a.n_jobs * sizeof(JobRec) +
                           (size_t)a.n_bvh_total * sizeof(BvhNode) + (a.jobs ? 0 : kHotLdsBytes) +
                           (a.has_cam0 ? sizeof(CameraArgs) : 0);
-    const size_t per_wave = (size_t)cand_slots(a) * 256 + align16((size_t)stack_slots(a) * 64 * stack_slot_bytes(a)) +
+    const size_t per_wave = (size_t)cand_slots(a) * kCandEntryBytes + align16((size_t)stack_slots(a) * 64 * stack_slot_bytes(a)) +
                             (size_t)a.nest_levels * 64 * 16;
     return shared + per_wave * waves_per_block;
 }
@@ -442,14 +444,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
     if (a.has_cam0) p += sizeof(CameraArgs);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = threadIdx.x >> 6;
-    const size_t ent_bytes = (size_t)cand_slots(a) * 256;
+    const size_t ent_bytes = (size_t)cand_slots(a) * kCandEntryBytes;
     const size_t stack_bytes = (size_t)stack_slots(a) * 64 * (kWide ? 5 : 4);
     const size_t per_wave = ent_bytes + stack_bytes + (size_t)a.nest_levels * 64 * 16;
     unsigned char* wp = p + per_wave * wave;
-    // candidate list, entry k at lst[k * 64]: a lower bound of the entry t
-    // (its upper 21 bits) and the candidate's place in the job's list, so
-    // that the smallest word is the nearest
-    uint32_t* lst = reinterpret_cast<uint32_t*>(wp) + lane;
+    // candidate list: entry k is entered at lstt[k * 64] or later, its place
+    // in the job's list is lstc[k * 64]
+    float* lstt = reinterpret_cast<float*>(wp) + lane;
+    uint16_t* lstc = reinterpret_cast<uint16_t*>(wp + (size_t)cand_slots(a) * 256) + lane;
     // traversal stack, slot l: the node word at stkc[l * 64]; kWide: the
     // child start there and the child mask at stkm[l * 64]
     uint32_t* stkc = reinterpret_cast<uint32_t*>(wp + ent_bytes) + lane;
@@ -782,7 +784,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
     auto list_candidate = [&](uint32_t c) {
         float t0;
         if (sphere_may_hit(lds_sph[fbase + c], r, tl) && may_enter(lds_frames[lds_cand[cbase + c]], r, tl, t0)) {
-            lst[n_lst * 64] = (__float_as_uint(fmaxf(t0, 0.f)) & ~kCandIndexMask) | c;
+            lstt[n_lst * 64] = t0;
+            lstc[n_lst * 64] = (uint16_t)c;
             ++n_lst;
         }
     };
@@ -1314,21 +1317,24 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
             if (n_lst == 0u) {
                 finish();
             } else {
-                uint32_t near = lst[0], at = 0;
+                float near = lstt[0];
+                uint32_t at = 0;
                 for (uint32_t k = 1; k < n_lst; ++k) {
-                    const uint32_t v = lst[k * 64];
-                    if (v < near) {
+                    const float v = lstt[k * 64];
+                    if (v < near || (v == near && lstc[k * 64] < lstc[at * 64])) {
                         near = v;
                         at = k;
                     }
                 }
+                const uint32_t c = lstc[at * 64];
                 --n_lst;
-                lst[at * 64] = lst[n_lst * 64];
-                if (__uint_as_float(near & ~kCandIndexMask) > fmaxf(tl, 0.f)) {
+                lstt[at * 64] = lstt[n_lst * 64];
+                lstc[at * 64] = lstc[n_lst * 64];
+                if (near > tl) {
                     n_lst = 0;   // the nearest lies beyond the best hit, and so do the others
                     if (c_next >= ncand) finish();
                     else --steps;   // (nothing was selected)
-                } else if (start_frame(lds_cand[cbase + (near & kCandIndexMask)])) {
+                } else if (start_frame(lds_cand[cbase + c])) {
                     mode = M_WALK;
                 } else {
                     // a frame that the walk's own entry test misses, which is

@@ -97,3 +97,26 @@ def test_parts_a_ray_passes_by_keep_its_last_hit(ctx, limit):
     assert int(again) == 0
     assert bool((out.id == -1).all())
     ctx.free_scene(h)
+
+
+def frames_walked(ctx, h, r):
+    import torch
+    out, counts, _ = ctx.trace_counted(h, torch.from_numpy(r).cuda())
+    torch.cuda.synchronize()
+    return out, counts[1].cpu().numpy()
+
+
+@pytest.mark.parametrize("near,hidden", [(3, 9), (9, 3)])
+def test_entries_that_differ_in_their_fifth_digit(ctx, limit, near, hidden):
+    """Entries are compared in 32 bits: the part that is 0.06 nearer at a
+    distance of 1,000 is walked first, and hides the other."""
+    far = [(200.0 + 40 * s, 100.0, 900.0) for s in range(12)]   # (the hierarchy's leaves come in order of x)
+    far[hidden] = (38.0, 40.0, 950.08)
+    far[near] = (40.0, 40.0, 950.02)
+    k = np.arange(64)
+    r = rays(np.stack([41.0 + k / 16.0, 41.0 + k / 32.0, np.full(64, -50.0)], 1), (0, 0, 1))
+    h = upload(ctx, parts(12, far))
+    out, frames = frames_walked(ctx, h, r)
+    assert bool((out.inst == near).all())
+    assert (frames == 1).all(), frames
+    ctx.free_scene(h)
