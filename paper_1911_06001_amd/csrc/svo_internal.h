@@ -52,8 +52,9 @@ constexpr uint32_t kMaxInlineNest = 4;
 // Candidates are tested one by one up to this many; beyond, they are found
 // through a bounding-box hierarchy.
 constexpr uint32_t kMaxSortedCand = 16;
-// A ray's list of candidates to walk holds this many at a time.
-constexpr uint32_t kCandList = 8;
+// A ray's list of candidates to walk holds this many at a time (most rays have
+// none to three; one with more lists the rest when these are done).
+constexpr uint32_t kCandList = 7;
 
 // One node of a frame table's hierarchy over its candidate frames, in
 // preorder: the world-space box of the moved root cells below it (widened

@@ -76,6 +76,7 @@ constexpr uint32_t kStepLimitId = 0xFFFFFFFEu;
 enum : uint32_t { M_DONE = 0, M_WALK = 1, M_SELECT = 2 };
 enum : uint32_t { EV_NONE = 0, EV_HIT = 1, EV_ENTER = 2, EV_END = 3, EV_LIMIT = 4 };
 enum : uint32_t { PEND_RESUME = 1, PEND_ROOT_HIT = 2 };
+constexpr uint32_t kUnlisted = ~0u, kListMore = 0x100u;
 
 struct Ray {
     float ox, oy, oz, tmin, dx, dy, dz, tmax;
@@ -376,12 +377,14 @@ __device__ __forceinline__ void gst(T* p, uint64_t i, T v) {
 
 }  // namespace
 
-// Per-lane candidate list in LDS: up to kCandList entries (most rays have
-// none to three; one with more lists the rest when these are done), an entry t
-// and the candidate's place in the job's list (16 bits) each.
+// Per-lane candidate list in LDS: kCandList entries and the one after which
+// the next list starts, an entry t and the candidate's place in the job's list
+// (16 bits) each.  A constant length, as every address that depends on one
+// read from the arguments costs a register in the kernel (1080p terrain 127.2
+// and 131.9 us, a batch of 8 jobs 355 and 370).
 constexpr uint32_t kCandEntryBytes = 64 * (4 + 2);   // of a wave
-__host__ __device__ __forceinline__ uint32_t cand_slots(const TraceArgs& a) {
-    return a.max_cand < kCandList ? a.max_cand : kCandList;
+__host__ __device__ __forceinline__ uint32_t cand_bytes(const TraceArgs& a) {
+    return a.max_cand ? (kCandList + 1u) * kCandEntryBytes : 0u;
 }
 
 // Traversal-stack slots per lane: slot sb + h holds the node whose children
@@ -394,7 +397,7 @@ size_t trace_lds_bytes(const TraceArgs& a, uint32_t waves_per_block) {
     const size_t shared = (size_t)a.n_frames * 80 + align16((size_t)a.n_cand_total * 4) + (size_t)a.n_jobs * sizeof(JobRec) +
                           (size_t)a.n_bvh_total * sizeof(BvhNode) + (a.jobs ? 0 : kHotLdsBytes) +
                           (a.has_cam0 ? sizeof(CameraArgs) : 0);
-    const size_t per_wave = (size_t)cand_slots(a) * kCandEntryBytes + align16((size_t)stack_slots(a) * 64 * stack_slot_bytes(a)) +
+    const size_t per_wave = cand_bytes(a) + align16((size_t)stack_slots(a) * 64 * stack_slot_bytes(a)) +
                             (size_t)a.nest_levels * 64 * 16;
     return shared + per_wave * waves_per_block;
 }
@@ -444,14 +447,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
     if (a.has_cam0) p += sizeof(CameraArgs);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = threadIdx.x >> 6;
-    const size_t ent_bytes = (size_t)cand_slots(a) * kCandEntryBytes;
+    const size_t ent_bytes = cand_bytes(a);
     const size_t stack_bytes = (size_t)stack_slots(a) * 64 * (kWide ? 5 : 4);
     const size_t per_wave = ent_bytes + stack_bytes + (size_t)a.nest_levels * 64 * 16;
     unsigned char* wp = p + per_wave * wave;
-    // candidate list: entry k is entered at lstt[k * 64] or later, its place
-    // in the job's list is lstc[k * 64]
-    float* lstt = reinterpret_cast<float*>(wp) + lane;
-    uint16_t* lstc = reinterpret_cast<uint16_t*>(wp + (size_t)cand_slots(a) * 256) + lane;
     // traversal stack, slot l: the node word at stkc[l * 64]; kWide: the
     // child start there and the child mask at stkm[l * 64]
     uint32_t* stkc = reinterpret_cast<uint32_t*>(wp + ent_bytes) + lane;
@@ -628,9 +627,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
     uint32_t best_id = kNone, best_inst = kNone;
     int best_f = -1, best_axis = 3;
     uint32_t steps = 0;
-    // the ray's candidates: entries in its list, and the first candidate
-    // not yet tested for it
-    uint32_t n_lst = 0, c_next = 0;
+    // the ray's candidate list: kUnlisted before it is made, then its length,
+    // and kListMore if more candidates than it holds may have been tested
+    uint32_t lst = kUnlisted;
+    // entry k of the list is entered at lstt[k * 64] or later, its place in
+    // the job's list is lstc[k * 64] (set where the list is used, so that the
+    // walk keeps no registers for them)
+    float* lstt = nullptr;
+    uint16_t* lstc = nullptr;
     FrameRay fr{};
     // the current cell: corner (px, py, pz), size 2^h, reached at tc0; pw is
     // the word of its parent node (mask in the low byte, child start above;
@@ -778,16 +782,33 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
         return true;
     };
 
-    // Test candidate c of the job for this ray and list it (the list has
-    // room).  By now the ray has its hit in the frames before, if any, so
-    // candidates behind it drop out.
-    auto list_candidate = [&](uint32_t c) {
-        float t0;
-        if (sphere_may_hit(lds_sph[fbase + c], r, tl) && may_enter(lds_frames[lds_cand[cbase + c]], r, tl, t0)) {
-            lstt[n_lst * 64] = t0;
-            lstc[n_lst * 64] = (uint16_t)c;
-            ++n_lst;
+    // Test candidate c of the job for this ray and put it on its list of n:
+    // of those tested, the nearest kCandList in order of entry and, where two
+    // are entered at the same t, of their place.  more: of those that come
+    // after entry kCandList.  By now the ray has its hit in the frames before,
+    // if any, so candidates behind it drop out.
+    auto list_candidate = [&](uint32_t c, bool more, uint32_t& n) {
+        float t;
+        if (!(sphere_may_hit(lds_sph[fbase + c], r, tl) && may_enter(lds_frames[lds_cand[cbase + c]], r, tl, t))) return;
+        if (more) {
+            const float from = lstt[kCandList * 64];
+            if (t < from || (t == from && c <= lstc[kCandList * 64])) return;
         }
+        uint32_t k = n;
+        if (k < kCandList) {
+            ++n;
+        } else {
+            // in place of the last of them, unless that comes before
+            k = 0;
+            for (uint32_t q = 1; q < kCandList; ++q) {
+                const float v = lstt[q * 64], w = lstt[k * 64];
+                if (v > w || (v == w && lstc[q * 64] > lstc[k * 64])) k = q;
+            }
+            const float w = lstt[k * 64];
+            if (t > w || (t == w && c > lstc[k * 64])) return;
+        }
+        lstt[k * 64] = t;
+        lstc[k * 64] = (uint16_t)c;
     };
 
     auto finish = [&]() {
@@ -1019,7 +1040,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
                     best_f = -1;
                     best_axis = 3;
                     steps = 0;
-                    n_lst = c_next = 0;
+                    lst = kUnlisted;
                     // a tile of the input list was traced by the wave it was dealt to
                     const bool dealt = !got_hot && ((cword >> (ctile & 31u)) & 1u);
                     bool keep = false;
@@ -1260,17 +1281,24 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
                 continue;
             }
             // ------------------------------------------------------ next candidate frame
-            // List the candidates the ray may enter before its best hit (the
-            // first time here, and again where the list was full): each by
-            // its bounding sphere (Sec. 4.1) and its root-cell entry.  Listing
-            // after the walk of the static world instead of when the ray was
-            // claimed lets that hit rule most of them out, and the list stays
-            // short (1080p terrain: 0.08 entries per ray for 8 candidates).
-            if (n_lst == 0u && c_next < ncand) {
-                const uint32_t slots = cand_slots(a);
+            // List the candidates the ray may enter before its best hit, the
+            // nearest first (the first time here, and again past a full list):
+            // each by its bounding sphere (Sec. 4.1) and its root-cell entry.
+            // Listing after the walk of the static world instead of when the
+            // ray was claimed lets that hit rule most of them out, and the
+            // list stays short (1080p terrain: 0.08 entries per ray for 8
+            // candidates).
+            uint32_t l = lane;
+            opaque(l);
+            lstt = reinterpret_cast<float*>(wp) + l;
+            lstc = reinterpret_cast<uint16_t*>(wp + (kCandList + 1u) * 256u) + l;
+            uint32_t n = lst & 0xFFu;
+            if (lst == kUnlisted || lst == kListMore) {
+                const bool more = lst == kListMore;
+                n = 0;
                 if constexpr (kSorted) {
-                    for (; c_next < ncand && n_lst < slots; ++c_next) list_candidate(c_next);
-                } else {
+                    for (uint32_t c = 0; c < ncand; ++c) list_candidate(c, more, n);
+                } else if (ncand) {
                     // The job's box hierarchy in preorder, one node for all
                     // of the wave's lanes that are here (of the same job) at a
                     // time: a node that no lane's ray meets is skipped with
@@ -1285,8 +1313,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
                         if (kSingle || job == j) {
                             const BoxRay br = box_ray(r);
                             const BvhNode* bvh = lds_bvh + uniform_u32(lds_jobs[j].bvh_base);
-                            const uint32_t end = uniform_u32(bvh_end(bvh[0])), first = c_next;
-                            c_next = ncand;
+                            const uint32_t end = uniform_u32(bvh_end(bvh[0]));
                             for (uint32_t i = 0; i < end;) {
                                 const BvhNode& N = bvh[i];
                                 const uint32_t na = uniform_u32(N.a), nb = uniform_u32(N.b);
@@ -1297,15 +1324,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
                                     continue;
                                 }
                                 if (leaf) {
-                                    // candidates come in ascending order; the
-                                    // first one that finds the list full is
-                                    // where the next listing starts
-                                    for (uint32_t c = na; c < na + (nb & 0xFFFFu); ++c) {
-                                        if (hit && c >= first && c_next == ncand) {
-                                            if (n_lst < slots) list_candidate(c);
-                                            else c_next = c;
-                                        }
-                                    }
+                                    for (uint32_t c = na; c < na + (nb & 0xFFFFu); ++c)
+                                        if (hit) list_candidate(c, more, n);
                                 }
                                 ++i;
                             }
@@ -1313,28 +1333,33 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
                         }
                     }
                 }
+                lst = (n == kCandList && n < ncand) ? kListMore : 0u;
             }
-            if (n_lst == 0u) {
+            float near = INFINITY;
+            uint32_t at = 0;
+            for (uint32_t k = 0; k < n; ++k) {
+                const float v = lstt[k * 64];
+                if (v < near || (v == near && lstc[k * 64] < lstc[at * 64])) {
+                    near = v;
+                    at = k;
+                }
+            }
+            if (n == 0u || near > tl) {
+                // none left, or the nearest lies beyond the best hit, and so
+                // do the others
                 finish();
             } else {
-                float near = lstt[0];
-                uint32_t at = 0;
-                for (uint32_t k = 1; k < n_lst; ++k) {
-                    const float v = lstt[k * 64];
-                    if (v < near || (v == near && lstc[k * 64] < lstc[at * 64])) {
-                        near = v;
-                        at = k;
-                    }
-                }
                 const uint32_t c = lstc[at * 64];
-                --n_lst;
-                lstt[at * 64] = lstt[n_lst * 64];
-                lstc[at * 64] = lstc[n_lst * 64];
-                if (near > tl) {
-                    n_lst = 0;   // the nearest lies beyond the best hit, and so do the others
-                    if (c_next >= ncand) finish();
-                    else --steps;   // (nothing was selected)
-                } else if (start_frame(lds_cand[cbase + c])) {
+                --n;
+                lstt[at * 64] = lstt[n * 64];
+                lstc[at * 64] = lstc[n * 64];
+                lst = (lst & kListMore) | n;
+                if (lst == kListMore) {
+                    // the next list starts after this one
+                    lstt[kCandList * 64] = near;
+                    lstc[kCandList * 64] = (uint16_t)c;
+                }
+                if (start_frame(lds_cand[cbase + c])) {
                     mode = M_WALK;
                 } else {
                     // a frame that the walk's own entry test misses, which is

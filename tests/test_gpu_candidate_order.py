@@ -120,3 +120,31 @@ def test_entries_that_differ_in_their_fifth_digit(ctx, limit, near, hidden):
     assert bool((out.inst == near).all())
     assert (frames == 1).all(), frames
     ctx.free_scene(h)
+
+
+@pytest.mark.parametrize("n", [11, 22, 60])      # over one, three and eight lists of seven
+def test_the_nearest_of_a_row_is_walked_first(ctx, limit, n):
+    """Rays against a row of n parts, whose list runs from the far end: each
+    walks the nearest one and no other.  From the middle of the row too, where
+    half of it lies behind."""
+    h = upload(ctx, parts(n, [(50.0 + 10 * s, 40.0, 40.0) for s in range(n)]))
+    k = np.arange(64)
+    for x0, inst in ((100.0 + 10 * n, n - 1), (50.0 + 10 * (n // 2) - 1.0, n // 2 - 1)):
+        o = np.stack([np.full(64, x0), 41.0 + k / 16.0, 41.0 + k / 32.0], 1)
+        out, frames = frames_walked(ctx, h, rays(o, (-1, 0, 0)))
+        assert bool((out.inst == inst).all())
+        assert (frames == 1).all(), (x0, frames)
+    ctx.free_scene(h)
+
+
+@pytest.mark.parametrize("n", [11, 14, 15, 60])
+def test_parts_entered_at_the_same_t_are_walked_once(ctx, limit, n):
+    """Rays that start inside the empty halves of n overlapping parts and leave
+    without a hit: every part is entered at tmin, and walked exactly once."""
+    h = upload(ctx, parts(n, [(40.0 + 0.01 * s, 40.0, 40.0) for s in range(n)]))
+    k = np.arange(64)
+    o = np.stack([43.0 + k / 32.0, 43.0 + k / 64.0, np.full(64, 46.0)], 1)
+    out, frames = frames_walked(ctx, h, rays(o, (0, 0.01, 1)))
+    assert bool((out.id == -1).all())
+    assert (frames == n).all(), frames
+    ctx.free_scene(h)
