@@ -5,6 +5,7 @@ one and through the box hierarchy (needs the GPU)."""
 import numpy as np
 import pytest
 
+import parity
 from svogen import scenes
 
 pytestmark = pytest.mark.gpu
@@ -147,4 +148,33 @@ def test_parts_entered_at_the_same_t_are_walked_once(ctx, limit, n):
     out, frames = frames_walked(ctx, h, rays(o, (0, 0.01, 1)))
     assert bool((out.id == -1).all())
     assert (frames == n).all(), frames
+    ctx.free_scene(h)
+
+
+def test_rays_from_anywhere_against_many_parts(ctx, oracle_lib):
+    """Waves of unrelated rays, and of rays of several jobs, each finding its
+    own way through the hierarchy over more than a hundred parts."""
+    import torch
+    from paper_1911_06001_amd import svo
+    sc = scenes.tiny_scene(41, K=6, n_slots=120, nested=False, scale_range=(1.0, 3.0))
+    assert sc.n_slots > 100
+    r = scenes.random_rays(13, 3000, 0, 64)
+    n = r.shape[0]
+    h = upload(ctx, sc)
+    dev = torch.from_numpy(r).cuda()
+    new = lambda: svo.Hits(torch.full((n,), -7, dtype=torch.int32, device="cuda"),
+                           torch.full((n,), -7, dtype=torch.int32, device="cuda"),
+                           torch.full((n,), -7.0, device="cuda"), torch.full((n, 3), -7.0, device="cuda"))
+    one, many = new(), new()
+    ctx.trace_into(h, dev, one.id, one.t, one.inst, one.normal)
+    cuts = [0, 1, 3, 20, 50, 51, 130, 700, 705, 1999, n]
+    ctx.trace_batch([dict(scene=h, rays=dev[a:b], out_id=many.id[a:b], out_inst=many.inst[a:b], out_t=many.t[a:b],
+                          out_normal=many.normal[a:b]) for a, b in zip(cuts, cuts[1:])])
+    torch.cuda.synchronize()
+    for k in ("id", "inst", "t", "normal"):
+        assert torch.equal(getattr(one, k), getattr(many, k)), k
+    ref = oracle_lib.trace_scene(sc, r, margin=True)
+    st = parity.compare(parity.to_numpy(one), ref, ref.margin, r)
+    parity.assert_parity(st)
+    assert st["hits"] > 1000
     ctx.free_scene(h)
