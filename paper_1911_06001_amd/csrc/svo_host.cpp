@@ -1246,7 +1246,8 @@ void write_tables(const Packing& P, svo::JobRec* jr, svo::FrameRec* fr, uint32_t
         const Scene& S = *Q.S;
         const unsigned char* tab = Q.table.empty() ? S.h_stage[S.cur] : Q.table.data();
         std::memcpy(fr + Q.frame_base, tab, (size_t)S.n_frames * sizeof(svo::FrameRec));
-        std::memcpy(sr + 4 * (size_t)Q.frame_base, tab + sphere_offset(S.n_frames, S.n_slots), (size_t)S.n_frames * 16);
+        std::memcpy(sr + 4 * (size_t)Q.cand_base, tab + sphere_offset(S.n_frames, S.n_slots),
+                    (size_t)(Q.T.n_cand + Q.T.n_inline) * 16);
         std::memcpy(xr + (size_t)svo::kExactMapDoubles * Q.frame_base, tab + xmap_offset(S.n_frames, S.n_slots),
                     (size_t)S.n_frames * kXmapBytes);
         const uint32_t* sc = reinterpret_cast<const uint32_t*>(tab + cand_offset(S.n_frames));

@@ -250,8 +250,8 @@ struct TraceArgs {
     JobRec job0;
     const FrameRec* frames;   // n_frames records; job j's slot s is frames[frame_base_j + 1 + s]
     const uint32_t* cand;     // candidate frames (absolute indices), per job contiguous
-    const float4* spheres;    // per job, n_frames entries: world bounding spheres of the moved root cells of the job's
-                              // listed frames, in list order (centre, square of the radius inflated by 1e-4)
+    const float4* spheres;    // per entry of cand (and of the in-place frames after a job's candidates): the world
+                              // bounding sphere of its moved root cell (centre, square of the radius inflated by 1e-4)
     const double* xmaps;      // n_frames exact maps (kExactMapDoubles each), indexed like frames
     const BvhNode* bvh;       // n_bvh_total hierarchy nodes, per job contiguous (job j's root at bvh_base_j)
     uint32_t n_bvh_total;

@@ -391,8 +391,8 @@ __host__ __device__ __forceinline__ uint32_t stack_slots(const TraceArgs& a) { r
 __host__ __device__ __forceinline__ uint32_t stack_slot_bytes(const TraceArgs& a) { return a.wide ? 5u : 4u; }
 
 size_t trace_lds_bytes(const TraceArgs& a, uint32_t waves_per_block) {
-    const size_t shared = (size_t)a.n_frames * 80 + align16((size_t)a.n_cand_total * 4) + (size_t)a.n_jobs * sizeof(JobRec) +
-                          (size_t)a.n_bvh_total * sizeof(BvhNode) + (a.jobs ? 0 : kHotLdsBytes) +
+    const size_t shared = (size_t)a.n_frames * sizeof(FrameRec) + (size_t)a.n_cand_total * 16 +
+                          align16((size_t)a.n_cand_total * 2) + (size_t)a.n_jobs * sizeof(JobRec) + (size_t)a.n_bvh_total * sizeof(BvhNode) + (a.jobs ? 0 : kHotLdsBytes) +
                           (a.has_cam0 ? sizeof(CameraArgs) : 0);
     const size_t per_wave = cand_bytes(a) + align16((size_t)stack_slots(a) * 64 * stack_slot_bytes(a)) +
                             (size_t)a.nest_levels * 64 * 16;
@@ -427,9 +427,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
     FrameRec* lds_frames = reinterpret_cast<FrameRec*>(p);
     p += (size_t)a.n_frames * 64;
     float4* lds_sph = reinterpret_cast<float4*>(p);
-    p += (size_t)a.n_frames * 16;
-    uint32_t* lds_cand = reinterpret_cast<uint32_t*>(p);
-    p += align16((size_t)a.n_cand_total * 4);
+    p += (size_t)a.n_cand_total * 16;
+    uint16_t* lds_cand = reinterpret_cast<uint16_t*>(p);
+    p += align16((size_t)a.n_cand_total * 2);
     JobRec* lds_jobs = reinterpret_cast<JobRec*>(p);
     p += (size_t)a.n_jobs * sizeof(JobRec);
     BvhNode* lds_bvh = reinterpret_cast<BvhNode*>(p);
@@ -501,8 +501,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
         uint4* dst = reinterpret_cast<uint4*>(lds_frames);
         for (uint32_t i = threadIdx.x; i < n_frames * 4u; i += blockDim.x) dst[i] = src[i];
     }
-    for (uint32_t i = threadIdx.x; i < n_frames; i += blockDim.x) lds_sph[i] = src_sph[i];
-    for (uint32_t i = threadIdx.x; i < n_cand_total; i += blockDim.x) lds_cand[i] = src_cand[i];
+    for (uint32_t i = threadIdx.x; i < n_cand_total; i += blockDim.x) {
+        lds_sph[i] = src_sph[i];
+        lds_cand[i] = (uint16_t)src_cand[i];   // a launch holds at most 2047 frames
+    }
     {
         const uint4* src = reinterpret_cast<const uint4*>(a.bvh);
         uint4* dst = reinterpret_cast<uint4*>(lds_bvh);
@@ -741,7 +743,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
         // entry (leaf entries never precede it); c: place in the job's list
         auto may_reach = [&](uint32_t c, float tlim) -> bool {
             float t0;
-            return sphere_may_hit(lds_sph[fbase + c], r, tlim) && may_enter(lds_frames[lds_cand[cbase + c]], r, tlim, t0);
+            return sphere_may_hit(lds_sph[cbase + c], r, tlim) && may_enter(lds_frames[lds_cand[cbase + c]], r, tlim, t0);
         };
         const JobRec& J = lds_jobs[job];
         if (!J.out_inst) return false;
@@ -786,7 +788,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
     // if any, so candidates behind it drop out.
     auto list_candidate = [&](uint32_t c, bool more, uint32_t& n) {
         float t;
-        if (!(sphere_may_hit(lds_sph[fbase + c], r, tl) && may_enter(lds_frames[lds_cand[cbase + c]], r, tl, t))) return;
+        if (!(sphere_may_hit(lds_sph[cbase + c], r, tl) && may_enter(lds_frames[lds_cand[cbase + c]], r, tl, t))) return;
         if (more) {
             const float from = lstt[kCandList * 64];
             if (t < from || (t == from && c <= lstc[kCandList * 64])) return;

@@ -178,3 +178,34 @@ def test_rays_from_anywhere_against_many_parts(ctx, oracle_lib):
     parity.assert_parity(st)
     assert st["hits"] > 1000
     ctx.free_scene(h)
+
+
+def test_a_batch_of_1998_frame_records_fits(ctx):
+    """Two jobs of 999 frame records, eight of them candidates found through
+    the hierarchy: tables that leave room for one wave's state."""
+    import copy
+
+    import torch
+    from paper_1911_06001_amd import svo
+    n, slots = 8, 998
+    sc = copy.copy(parts(n, [(50.0 + 10 * s, 40.0, 40.0) for s in range(n)]))
+    fwd = np.tile(np.eye(3, 4, dtype=np.float32).reshape(1, 12), (slots, 1))
+    fwd[:n] = sc.xform(0)
+    sc.slot_child = np.concatenate([sc.slot_child, np.zeros(slots - n, np.uint32)])
+    sc.slot_cell = np.concatenate([sc.slot_cell, np.ones((slots - n, 4), np.float32)])
+    k = np.arange(64)
+    r = torch.from_numpy(rays(np.stack([np.full(64, 300.0), 41.0 + k / 16.0, 41.0 + k / 32.0], 1), (-1, 0, 0))).cuda()
+    h = ctx.upload_scene(sc)
+    ctx.set_transforms(h, fwd)
+    assert ctx.scene_stats(h).n_candidates == n
+    ctx.set_config(sorted_candidates=1)
+    out = [svo.Hits(torch.full((64,), -7, dtype=torch.int32, device="cuda"),
+                    torch.full((64,), -7, dtype=torch.int32, device="cuda"),
+                    torch.full((64,), -7.0, device="cuda"), None) for _ in range(2)]
+    ctx.trace_batch([dict(scene=h, rays=r, out_id=o.id, out_inst=o.inst, out_t=o.t) for o in out])
+    torch.cuda.synchronize()
+    ctx.set_config(sorted_candidates=0)
+    for o in out:
+        assert bool((o.inst == n - 1).all())
+        assert bool((o.t == 300.0 - 50.0 - 10.0 * (n - 1) - CELL).all())
+    ctx.free_scene(h)
