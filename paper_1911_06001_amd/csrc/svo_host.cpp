@@ -1054,16 +1054,14 @@ uint64_t tile_stride(uint64_t tiles) {
 }
 
 // Fit a launch into the per-work-group LDS limit: take waves out of the
-// work-group (to the next multiple of 4, so the four SIMDs stay evenly
-// loaded, then one at a time).  Results never depend on them; a configuration
-// tuned on one scene may meet a batch whose tables are larger.  Returns the
-// LDS bytes, above the limit if nothing fits.
+// work-group, one at a time (1,000 candidates leave room for 7 of 8 waves:
+// 1280x720 primary rays 452 us with 7, 497 with 6, 653 with 4, the next
+// number that loads the four SIMDs evenly).  Results never depend on them; a
+// configuration tuned on one scene may meet a batch whose tables are larger.
+// Returns the LDS bytes, above the limit if nothing fits.
 size_t fit_lds(const svo_ctx* ctx, const svo::TraceArgs& a, uint32_t& waves) {
     size_t lds = svo::trace_lds_bytes(a, waves);
-    while (lds > ctx->max_lds && waves > 1) {
-        waves = (waves > 4 && waves % 4) ? waves & ~3u : (waves > 4 ? waves - 4 : waves - 1);
-        lds = svo::trace_lds_bytes(a, waves);
-    }
+    while (lds > ctx->max_lds && waves > 1) lds = svo::trace_lds_bytes(a, --waves);
     return lds;
 }
 
