@@ -131,7 +131,8 @@ typedef struct {
                                    against them one by one, one with more through the box hierarchy over their
                                    world boxes; both trace them in order of entry (the depth sort of Sec. 4.2).
                                    A scene whose table travels in the kernel arguments is always tested one by
-                                   one; a launch of several jobs, or a plan, goes by the context's value */
+                                   one; a launch of several jobs, or a plan, goes by the larger of the
+                                   context's value and its own configuration's (a tuned scene's) */
     uint32_t tile_order;        /* 0: slow tiles first, 1: the plain claim order.  With 0, a one-job trace with
                                    whole-tile claims (refill_lanes 0 or 64; not the hit buffer) lists the 64-ray
                                    tiles whose slowest ray took the most walk steps (about the slowest 12 %) in

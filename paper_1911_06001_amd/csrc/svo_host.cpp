@@ -417,6 +417,17 @@ uint32_t sort_limit(const svo_config& c) {
     return c.sorted_candidates ? c.sorted_candidates : svo::kMaxSortedCand;
 }
 
+// The same for a launch of several jobs, or a plan, whose configuration `c`
+// may be what svo_tune found for one scene alone.  Where that is the
+// hierarchy it says little about several jobs, whose kernels differ more (a
+// batch of 8 sphere and terrain jobs: 353 us one by one, 431 us through the
+// hierarchy that the terrain's tuning had picked).  Where it is one by one it
+// counts: the tables then need no room for hierarchies, without which many
+// jobs of such a scene would not fit the LDS.
+uint32_t batch_sort_limit(const svo_config& context, const svo_config& c) {
+    return std::max(sort_limit(context), sort_limit(c));
+}
+
 void free_scene(Scene& s) {
     if (s.d_nodes) (void)hipFree(s.d_nodes);
     for (int k = 0; k < 2; ++k) {
@@ -1485,12 +1496,7 @@ int trace_batch(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, void* stream
         const size_t cb = bb + (size_t)P.bvh * sizeof(svo::BvhNode);
         const size_t bytes = cb + P.jobs.size() * sizeof(svo::CameraArgs);
         svo::TraceArgs a{};
-        // one by one or through the hierarchy: what svo_tune found for one
-        // scene alone says little about a launch of several jobs, whose
-        // kernels differ more (a batch of 8 sphere and terrain jobs: 353 us
-        // one by one, 431 us when the terrain's tuning had picked the
-        // hierarchy), so those go by the context's limit
-        const bool sorted = P.max_cand <= sort_limit(P.jobs.size() > 1 ? ctx->cfg : cfg);
+        const bool sorted = P.max_cand <= (P.jobs.size() > 1 ? batch_sort_limit(ctx->cfg, cfg) : sort_limit(cfg));
         a.n_bvh_total = sorted ? 0u : P.bvh;
         a.n_jobs = (uint32_t)P.jobs.size();
         a.n_frames = P.frames;
@@ -1652,7 +1658,7 @@ int svo_plan_create(svo_ctx* ctx, const svo_scene* scenes, uint32_t n_scenes, co
         pl->off_sph = (pl->off_cand + (size_t)pl->max_frames * sizeof(uint32_t) + 15) & ~(size_t)15;
         pl->off_x = pl->off_sph + (size_t)pl->max_frames * 16;
         pl->off_bvh = pl->off_x + (size_t)pl->max_frames * kXmapBytes;
-        pl->max_bvh = pl->max_cand > sort_limit(ctx->cfg) ? 2 * pl->max_frames : 0u;   // as for a batch of jobs
+        pl->max_bvh = pl->max_cand > batch_sort_limit(ctx->cfg, pl->cfg) ? 2 * pl->max_frames : 0u;
         pl->off_cams = pl->off_bvh + (size_t)pl->max_bvh * sizeof(svo::BvhNode);
         pl->bytes = pl->off_cams + (size_t)pl->max_jobs * sizeof(svo::CameraArgs);
 
