@@ -199,6 +199,33 @@ constexpr uint32_t kHotPerBlock = kHotLdsBytes / 4 - kHotLdsHdr;
 static_assert(kHotLdsPtr + 2 <= kHotLdsHdr, "slow-tile LDS header too small");
 constexpr uint32_t kHotInitialThreshold = 64;
 
+#ifdef __HIPCC__
+#define SVO_HD __host__ __device__
+#else
+#define SVO_HD
+#endif
+
+// The next entry that a work-group deals out, kHotNone when it has none left:
+// its k-th claim (claim() counts them) takes entry (k / wpb) W + block wpb +
+// k mod wpb, W = blocks wpb, so that the first W entries go one to each wave
+// of the grid in work-group order.  Entry e is sub-list e mod kHotSub's
+// (e / kHotSub)-th, up to n_deal, kHotSub times the longest sub-list's count;
+// a claim that falls past the end of a shorter one goes on to the next.  So
+// every entry is dealt as long as a wave that gets none is the first to stop
+// asking: the regular order skips the tiles of the list, and a work-group
+// that starts when the queue is dry has nothing else to keep its waves.
+constexpr uint32_t kHotNone = 0xFFFFFFFFu;
+template <typename Claim>
+SVO_HD inline uint32_t hot_deal(Claim&& claim, uint32_t wpb, uint32_t blocks, uint32_t block, uint32_t n_deal,
+                                const uint32_t* cnt) {
+    for (;;) {
+        const uint32_t k = claim();
+        const uint64_t e = (uint64_t)(k / wpb) * blocks * wpb + (uint64_t)block * wpb + k % wpb;
+        if (e >= n_deal) return kHotNone;
+        if ((uint32_t)e / kHotSub < cnt[(uint32_t)e % kHotSub]) return (uint32_t)e;
+    }
+}
+
 constexpr size_t kStaticQueueBytes = ((size_t)kQueueWords * 4 + 255) & ~(size_t)255;
 constexpr size_t kStaticTableBytes = (size_t)256 << 10;
 constexpr size_t kStaticScratchBytes = kStaticQueueBytes + kStaticTableBytes;

@@ -874,17 +874,16 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
             }
             if (hin && rlo >= rhi) {
                 // the work-group's next entry, claimed by the leader for the
-                // wave (hin and the counts stay fixed during the launch):
-                // its k-th claim takes entry (k / wpb) W + blockIdx.x wpb +
-                // k mod wpb, W = n_active wpb, so that the first W entries
-                // go one to each wave of the grid in work-group order
-                uint32_t k = 0;
-                if (lane == leader) k = atomicAdd(lds_hot + kHotLdsTaken, 1u);
-                k = (uint32_t)__shfl((int)k, (int)leader);
-                const uint64_t e = (uint64_t)(k / wpb) * n_active * wpb + (uint64_t)blockIdx.x * wpb + k % wpb;
-                const uint32_t sub = (uint32_t)(e % kHotSub), i = (uint32_t)(e / kHotSub);
-                if (e < hin && i < lds_hot[kHotLdsCnt + sub]) {
+                // wave (hin and the counts stay fixed during the launch)
+                const auto claim_entry = [&]() -> uint32_t {
+                    uint32_t k = 0;
+                    if (lane == leader) k = atomicAdd(lds_hot + kHotLdsTaken, 1u);
+                    return (uint32_t)__builtin_amdgcn_readlane((int)k, (int)leader);
+                };
+                const uint32_t e = hot_deal(claim_entry, wpb, n_active, blockIdx.x, hin, lds_hot + kHotLdsCnt);
+                if (e != kHotNone) {
                     got_hot = true;
+                    const uint32_t sub = e % kHotSub, i = e / kHotSub;
                     const uint32_t ent = gld(hot_list(lds_hot_ptr(lds_hot), lds_hot[kHotLdsIn]), (uint64_t)sub * kHotSubCap + i);
                     htile = ent & kHotTileMask;
                     hcost = ent >> kHotTileBits;
