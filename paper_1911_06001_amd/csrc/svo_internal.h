@@ -115,10 +115,11 @@ constexpr uint32_t kMaxJobs = 256;
 // 128-byte line, then a bitmap of exhausted partitions, then the
 // finished-work-group counter.  Claims are interleaved over the partitions
 // (claim slot s belongs to partition s mod kQueueParts) so that no single
-// address serialises them; a wave starts on its own partition with a claim
-// that needs no counter, the wave that takes a partition's last claim marks
-// it in the bitmap, and a wave that finds a partition dry moves on to the
-// next one the bitmap still shows as open.
+// address serialises them; a wave starts on its own partition, the wave that
+// takes a partition's last claim marks it in the bitmap, and a wave that finds
+// a partition dry moves on to the next one the bitmap still shows as open.  A
+// launch of at most half the work-groups that may reside gives each wave one
+// claim by its index and leaves the queue alone.
 constexpr uint32_t kQueueParts = 64;
 constexpr uint32_t kQueueStride = 32;                              // uint32 words between counters
 constexpr uint32_t kQueueDry = kQueueParts * kQueueStride;         // 2 words: bitmap of dry partitions
@@ -290,7 +291,8 @@ struct TraceArgs {
     uint32_t* queue;          // kQueueWords: partition counters, then finished work-groups
     uint32_t stack_levels;    // traversal stack entries per lane
     uint32_t nest_levels;     // frame stack entries per lane (inline frames)
-    uint32_t max_blocks;      // work-groups of this launch's size that can be resident on the device
+    uint32_t max_blocks;      // work-groups of the persistent grid: as many as the configuration, the LDS and 32 waves
+                              // per CU let reside (registers may hold some of them back)
     uint32_t wide;            // 1: some pool has more than kPackedNodes nodes
     uint32_t sort_cand;       // 1: candidates tested one by one, 0: through the hierarchy
     uint32_t refill;          // a wave claims new rays once this many lanes are idle (1..64)

@@ -576,28 +576,23 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
     };
     const uint32_t wave_id = blockIdx.x * wpb + wave;
     uint32_t q = wave_id % kQueueParts, rlo = 0, rhi = 0;
-    // In a launch of at most half the work-groups that can be resident, a
-    // wave's first claim is fixed: claim wave_id / kQueueParts of its own
-    // partition, and the counters count on from the fixed ones.  Such a launch
-    // is over in the time of a tile or two, and a few atomic round trips (about
-    // 0.8 us each) to claim a tile and to find the rest claimed are a good part
-    // of that (256x256 rays: 26.5 us fixed, 29.7 by the counters; 100 rays 37.5
-    // and 40.5).  A larger one gains nothing by it (1080p: 157.5 either way),
-    // and where another stream's launch still holds part of the device, its
-    // last work-groups start late: tiles kept for them would wait.
+    // A launch of at most half the work-groups that its configuration lets
+    // reside has a wave for every tile: wave w takes claim slot w, and the
+    // queue is not used.  Such a launch is over in the time of a tile or two,
+    // and a few atomic round trips (about 0.8 us each) to claim a tile and to
+    // find the rest claimed are a good part of that (256x256 rays: 26.5 us
+    // fixed, 29.7 by the counters; 100 rays 37.5 and 40.5).  A larger one
+    // gains nothing by it (1080p: 157.5 either way), and where another
+    // stream's launch still holds part of the device, its last work-groups
+    // start late: tiles kept for them would wait.
     const bool fixed = 2u * n_active <= a.max_blocks;
-    auto fixed_len = [&](uint32_t p) -> uint32_t {
-        return fixed ? (n_waves / kQueueParts + (p < n_waves % kQueueParts ? 1u : 0u)) * claim : 0u;
-    };
-    if (fixed) {
-        rhi = part_len(q);
-        rlo = min(wave_id / kQueueParts * claim, rhi);
-        rhi = min(rlo + claim, rhi);
+    uint64_t known_dry = ~0ull;   // partitions this wave knows to be dry
+    if (!fixed) {
+        known_dry = __ballot(part_len(lane) == 0u);
+    } else if (wave_id < n_tiles) {
+        rlo = wave_id / kQueueParts * 64u;
+        rhi = rlo + 64u;
     }
-    // partitions this wave knows to be dry: here those that the fixed claims
-    // cover (one lane per partition)
-    uint64_t known_dry = __ballot(fixed_len(lane) >= part_len(lane));
-    const bool queue_used = known_dry != ~0ull;   // launch-wide: some partition has claims left
     // The tile that claim slot s covers: (s tstride) mod n_tiles, exactly (the
     // product stays below 2^53 and the quotient is off by at most one), in 15
     // instructions where the integer remainder takes about 80.
@@ -911,7 +906,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
                     len = part_len(q);
                     if (lane == leader) {
                         uint32_t* bm = a.queue + kQueueDry;
-                        base = fixed_len(q) + atomicAdd(a.queue + q * kQueueStride, claim);
+                        base = atomicAdd(a.queue + q * kQueueStride, claim);
                         if (base >= len)
                             dry = (uint64_t)__hip_atomic_load(bm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) |
                                   ((uint64_t)__hip_atomic_load(bm + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) << 32);
@@ -1357,7 +1352,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
     // the last work-group out resets the queue for the next launch; only
     // work-groups that may claim count (an idle one of a plan's fixed grid
     // touches no counter, and skipping its atomic spares the others a
-    // same-address queue), and none where the fixed claims were all.  Every
+    // same-address queue), and none in a launch that used no counter.  Every
     // word that another work-group reads here is written by atomics, so all
     // that has to come before the count is their completion: each wave waits
     // for its own, and no cache is written back or invalidated (a device
@@ -1384,7 +1379,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
             }
         }
     }
-    if (active && (queue_used || hot) && threadIdx.x == 0) {
+    if (active && !fixed && threadIdx.x == 0) {
         wait_memory();
         uint32_t* fin = a.queue + kQueueFinished;
         const uint32_t prev = atomicAdd(fin, 1u);
