@@ -15,7 +15,6 @@
 #include <new>
 #include <numeric>
 #include <set>
-#include <string>
 #include <vector>
 
 #include "svo.h"
@@ -23,15 +22,13 @@
 
 namespace {
 
-thread_local std::string g_err;
+thread_local char g_err[512];   // (no allocation: it also reports that there is no memory)
 
 int fail(int code, const char* fmt, ...) {
-    char buf[512];
     va_list ap;
     va_start(ap, fmt);
-    vsnprintf(buf, sizeof buf, fmt, ap);
+    vsnprintf(g_err, sizeof g_err, fmt, ap);
     va_end(ap);
-    g_err = buf;
     return code;
 }
 
@@ -763,7 +760,7 @@ extern "C" {
 
 int svo_abi_version(void) { return SVO_ABI_VERSION; }
 
-const char* svo_last_error(void) { return g_err.c_str(); }
+const char* svo_last_error(void) { return g_err; }
 
 int svo_validate(const uint64_t* nodes, uint64_t n_nodes, uint32_t root, uint32_t max_depth,
                  const uint32_t* slot_child, uint32_t n_slots, svo_pool_info* info) {
@@ -874,8 +871,9 @@ int svo_upload(svo_ctx* ctx, const uint64_t* nodes, uint64_t n_nodes, uint32_t r
             if (!std::isfinite(slot_cell[4 * s + a])) return fail(SVO_EINVAL, "slot_cell[%u] must be finite", s);
         if (!(slot_cell[4 * s + 3] > 0.0f)) return fail(SVO_EINVAL, "slot_cell[%u] size must be > 0", s);
     }
+    std::unique_ptr<Scene> S;
     try {
-        std::unique_ptr<Scene> S(new Scene());
+        S.reset(new Scene());
         int rc = analyse(nodes, n_nodes, root, max_depth, slot_child, n_slots, S->an);
         if (rc) return rc;
         S->n_nodes = n_nodes;
@@ -931,6 +929,7 @@ int svo_upload(svo_ctx* ctx, const uint64_t* nodes, uint64_t n_nodes, uint32_t r
         *out = h;
         return SVO_OK;
     } catch (const std::bad_alloc&) {
+        if (S) free_scene(*S);   // device and pinned memory outlive a Scene
         return fail(SVO_ENOMEM, "out of host memory");
     }
 }
