@@ -209,3 +209,36 @@ def test_a_batch_of_1998_frame_records_fits(ctx):
         assert bool((o.inst == n - 1).all())
         assert bool((o.t == 300.0 - 50.0 - 10.0 * (n - 1) - CELL).all())
     ctx.free_scene(h)
+
+
+@pytest.mark.parametrize("m", [1, 2, 6, 7, 8, 13, 14, 15])
+def test_list_lengths_with_a_device_table(ctx, oracle_lib, limit, m):
+    """m parts that overlap and twelve far away, so that the table is too large
+    for the kernel arguments: rays that meet up to m of them, as a first trace
+    and as a re-trace after the parts moved (lists hold seven)."""
+    import torch
+    from paper_1911_06001_amd import svo
+    n = m + 12
+    at = [(40.0 + 0.6 * s, 40.0 + 0.3 * (s % 5), 40.0 + 0.2 * (s % 3)) for s in range(m)]
+    sc = parts(n, at + [(300.0 + 20 * s, 300.0, 300.0) for s in range(12)])
+    moved = sc.xform(0).copy()
+    moved.reshape(n, 3, 4)[:, :, 3] += 0.7
+    r = scenes.random_rays(m, 2000, 38.0, 52.0)
+    dev = torch.from_numpy(r).cuda()
+    h = upload(ctx, sc)
+    for fwd in (None, moved):
+        out = svo.Hits(torch.full((2000,), -7, dtype=torch.int32, device="cuda"),
+                       torch.full((2000,), -7, dtype=torch.int32, device="cuda"),
+                       torch.full((2000,), -7.0, device="cuda"), torch.full((2000, 3), -7.0, device="cuda"))
+        if fwd is None:
+            ctx.trace_into(h, dev, out.id, out.t, out.inst, out.normal)
+        else:
+            ctx.trace_into(h, dev, out.id, out.t, out.inst, out.normal)
+            ctx.set_transforms(h, fwd)
+            ctx.trace_reuse(h, dev, out)
+        torch.cuda.synchronize()
+        ref = oracle_lib.trace_scene(sc, r, fwd=fwd, margin=True)
+        st = parity.compare(parity.to_numpy(out), ref, ref.margin, r)
+        parity.assert_parity(st)
+        assert st["hits"] > 300
+    ctx.free_scene(h)

@@ -107,3 +107,39 @@ def test_packed_and_wide_pools_in_one_batch(ctx, oracle_lib, sorted_candidates):
     ctx.set_config(sorted_candidates=0)
     for _, h, _ in runs:
         ctx.free_scene(h)
+
+
+@pytest.mark.parametrize("path", ["one by one", "hierarchy"])
+@pytest.mark.parametrize("kind", ["inline", "candidates"])
+@pytest.mark.parametrize("n_nodes", [None, PACKED, PACKED + 1])
+def test_pool_sizes_with_a_device_table(ctx, oracle_lib, n_nodes, kind, path):
+    """One-job launches of 12 parts, whose table is too large for the kernel
+    arguments, on either candidate path of either word format."""
+    import torch
+    from paper_1911_06001_amd import svo
+    sc = scenes.tiny_scene(17, K=5, n_slots=12, nested=True, scale_range=(0.3, 0.5) if kind == "inline" else (0.8, 2.0))
+    assert sc.n_slots == 12
+    if n_nodes is not None:
+        sc = stretched(sc, n_nodes)
+    rays = scenes.random_rays(8, 3000, 0, 32)
+    n = rays.shape[0]
+    dev = torch.from_numpy(rays).cuda()
+    h = ctx.upload_scene(sc)
+    ctx.set_transforms(h, sc.xform(0))
+    st = ctx.scene_stats(h)
+    assert st.n_inline > 2 if kind == "inline" else st.n_candidates > 8
+    ctx.set_config(sorted_candidates=64 if path == "one by one" else 1)
+    out = svo.Hits(torch.full((n,), -7, dtype=torch.int32, device="cuda"),
+                   torch.full((n,), -7, dtype=torch.int32, device="cuda"),
+                   torch.full((n,), -7.0, device="cuda"), torch.full((n, 3), -7.0, device="cuda"))
+    ctx.trace_into(h, dev, out.id, out.t, out.inst, out.normal)
+    again, _, _ = ctx.trace_counted(h, dev)
+    torch.cuda.synchronize()
+    ctx.set_config(sorted_candidates=0)
+    for k in ("id", "inst", "t", "normal"):
+        assert torch.equal(getattr(out, k), getattr(again, k)), k
+    ref = oracle_lib.trace_scene(sc, rays, margin=True)
+    stats = parity.compare(parity.to_numpy(out), ref, ref.margin, rays)
+    parity.assert_parity(stats)
+    assert stats["hits"] > 300
+    ctx.free_scene(h)
