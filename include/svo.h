@@ -126,7 +126,8 @@ typedef struct {
                                    caches, which is faster than a copy of the pool's first nodes in LDS */
     uint32_t refill_lanes;      /* 0 or 64: a wave takes 64-ray tiles; 1..63: claim new rays once that many lanes are idle */
     uint32_t step_limit;        /* cell advances plus candidate selections per ray before SVO_STEP_LIMIT */
-    uint32_t claim_tiles;       /* 64-ray tiles a wave takes from the work queue at once (0: 2; at most 64) */
+    uint32_t claim_tiles;       /* 64-ray tiles a wave takes from the work queue at once (0: 2; at most 64); 1 in a
+                                   launch of fewer than two tiles a wave */
     uint32_t sorted_candidates; /* 0: 16; 1..64: a job with at most this many candidate frames tests each ray
                                    against them one by one, one with more through the box hierarchy over their
                                    world boxes; both trace them in order of entry (the depth sort of Sec. 4.2).
@@ -138,8 +139,9 @@ typedef struct {
                                    tiles whose slowest ray took the most walk steps (about the slowest 12 %) in
                                    its work queue's state, and the next trace of the same rays on the same
                                    stream hands those tiles to its waves first, so that the launch's longest
-                                   chains start at its beginning instead of setting its end.  Order only:
-                                   results are the same. */
+                                   chains start at its beginning instead of setting its end.  A launch
+                                   of at most one tile a wave starts them all at once and neither
+                                   keeps nor takes a list.  Order only: results are the same. */
 } svo_config;
 
 /* ABI version the library was built with (SVO_ABI_VERSION). */

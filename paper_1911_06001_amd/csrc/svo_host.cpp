@@ -899,7 +899,7 @@ int svo_upload(svo_ctx* ctx, const uint64_t* nodes, uint64_t n_nodes, uint32_t r
         }
         S->n_frames = 1 + n_slots;
         S->table_bytes = table_size(S->n_frames, n_slots);
-        // at most 16 slots: every candidate takes the sorted path, which
+        // at most 16 slots: every candidate is tested one by one, which
         // needs no hierarchy, so records, candidates, spheres and exact maps suffice
         S->inline_tab = n_slots <= svo::kMaxSortedCand && bvh_offset(S->n_frames, n_slots) <= svo::kInlineTableBytes;
         const size_t fb = S->table_bytes;
@@ -1243,7 +1243,7 @@ int pack_jobs(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, const std::set
 
 // Write job records, frame records, candidates (absolute frame indices),
 // spheres, exact maps and hierarchy nodes (skipped when br is null: launches
-// that take every candidate through the sorted path) of a packing into host
+// that test every candidate one by one) of a packing into host
 // memory.  Camera jobs get their camera at cams[i] (host), which the launch reads at
 // dev_cams + i.
 void write_tables(const Packing& P, svo::JobRec* jr, svo::FrameRec* fr, uint32_t* cr, float* sr, double* xr,

@@ -259,11 +259,9 @@ constexpr uint32_t kInlineTableBytes = 2048;
 // FP32 record; the entry t of the cell it hits is recomputed from this one.
 constexpr uint32_t kExactMapDoubles = 12;
 
-// In a plan launch (hdr != nullptr) n_jobs, n_frames, n_cand_total and
-// n_bvh_total are capacities that size the LDS layout, and the header holds
-// the counts; n_rays, tile_stride and tile_inv are ignored.
-// A launch whose pool, rays and hits together are larger than this reads its
-// rays with the streaming hint: they would only push nodes out of the L2s and
+// A one-job launch of a scene, or of its table in the arguments, whose pool,
+// rays and hits together are larger than this reads its rays with the
+// streaming hint: they would only push nodes out of the L2s and
 // the 256 MB last-level cache, and are gone from there before they are traced
 // again.  Without / with the hint, new cameras: terrain (18 MB pool) at
 // 2,822,400 rays (176 MB) 180 / 184 us, at 3,686,400 (225 MB) 225 / 217; at
@@ -272,6 +270,9 @@ constexpr uint32_t kExactMapDoubles = 12;
 // 406 / 389; terrain at 2,073,600 rays (134 MB) 154 / 161.
 constexpr uint64_t kStreamBytes = (uint64_t)192 << 20;
 
+// In a plan launch (hdr != nullptr) n_jobs, n_frames, n_cand_total and
+// n_bvh_total are capacities that size the LDS layout, and the header holds
+// the counts; n_rays, tile_stride and tile_inv are ignored.
 struct TraceArgs {
     const LaunchHdr* hdr;     // plan launches: counts in device memory; else nullptr
     const JobRec* jobs;       // device job table, or nullptr: the single job in job0

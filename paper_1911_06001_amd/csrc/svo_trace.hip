@@ -19,10 +19,10 @@
 //   5. transformed subtrees that leave their static cell are candidates,
 //      traced from their own roots in order of root-cell entry and skipped
 //      once it lies beyond the best hit (the depth sort of Sec. 4.2): after
-//      the walk of the world frame each ray lists those that it may enter
-//      before its hit, by the bounding-sphere test of Sec. 4.1 and the slab
-//      entry, up to 16 tested one by one, more through a hierarchy of their
-//      world boxes;
+//      the walk of the world frame each ray lists the nearest of those that
+//      it may enter before its hit, by the bounding-sphere test of Sec. 4.1
+//      and the slab entry, up to 16 tested one by one, more through a
+//      hierarchy of their world boxes;
 //   6. at the hit, recompute its entry t and face from the frame's FP64 map
 //      (the walk's FP32 entry t carries an error that grows with the
 //      coordinates); write id, slot, t and the normal (entry face, inverse
@@ -50,14 +50,14 @@
 // rate over a whole 1080p terrain launch under a moving camera, 83 % over a 4K
 // launch on the 4096^3 terrain), then the longest chains of dependent walk steps; memory only
 // through their latency (the 1080p terrain moves 116 MB of rays and hits in
-// 126 us).  So the walk is laid out for few instructions per step: one turn of
+// 127 us).  So the walk is laid out for few instructions per step: one turn of
 // its loop advances and then descends (14.4 turns per 64-ray tile where a turn
 // that did either took 19.5), node words come ready to push (absolute child
 // starts, encoded at upload), and the loop keeps no lane masks.  Together with
 // the queue, the candidate listing, the register budgets and the streaming
-// hints below: 1080p terrain under moving cameras 220 -> 149 us, the same rays
-// again 174 -> 126, 64 instances 375 -> 242, 4K on the 4096^3 terrain 2,176 ->
-// 1,478.
+// hints below: 1080p terrain under moving cameras 221 -> 150 us, the same rays
+// again 185 -> 129, 64 instances 398 -> 252, 4K on the 4096^3 terrain 2,159 ->
+// 1,482.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
@@ -404,11 +404,12 @@ size_t trace_lds_bytes(const TraceArgs& a, uint32_t waves_per_block) {
 // the two, and each instantiation carries only its own path.  All but one are
 // compiled for 6 resident waves per SIMD (80 VGPRs): the few values that then
 // go to scratch are per-ray state outside the walk loop, and the extra waves
-// hide more of the node-load latency.  (Hierarchy at its natural 106 VGPRs, 4
-// waves: instances 288 us, their AO rays 462; at 5 waves 273 and 435; at 6
-// waves 270 and 420.  One-by-one at 7 waves: 1080p terrain 139 us, at 6 waves
-// 128.)  The wide hierarchy one is compiled for 5 (96 VGPRs): 4096^3 terrain
-// 1,586 us at 4 waves, 1,564 at 5, 1,647 at 6, where it spills more.
+// hide more of the node-load latency.  (12 waves a work-group, 2 work-groups a
+// CU: hierarchy for 4 waves instances 309 us, their AO rays 490; for 5 waves
+// 312 and 494; for 6 waves 260 and 394.  One-by-one for 7 waves: 1080p terrain
+// 136 us, for 6 waves 126.)  The wide hierarchy one is compiled for 5 (96
+// VGPRs): 4096^3 terrain, tuned, 1,507 us at 4 waves, 1,501 at 5, 1,611 at 6,
+// where it spills more.
 // kSingle: a one-job launch (the job in the arguments), whose pool and table
 // offsets are then launch-wide values (scalar registers) rather than per-lane
 // ones.
@@ -1093,9 +1094,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
             // 12.1 and 12.9 times; a loop of one step (advance or descend) per
             // turn took 19.5 turns and 15.0 and 15.8 halves, and a second
             // advance per turn runs more instructions than it saves.  A turn
-            // is about 77 VALU instructions (about 115 with child offsets
-            // relative to the node, the child start and mask apart in the
-            // stack and the exit planes computed for both halves).  Measured
+            // that runs both halves is 87 VALU instructions (about 115 with
+            // child offsets relative to the node, the child start and mask
+            // apart in the stack and the exit planes computed for both
+            // halves).  Measured
             // against that loop: 1080p terrain animation 176 -> 145 us,
             // 4096^3 terrain at 4K 2,186 -> 1,846 us, 1080p instances 401 ->
             // 334 us, 256x256 sphere 64 -> 54 us.
@@ -1105,7 +1107,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kSorted ||
             // a lane that stops there computes a state that nothing reads.  As
             // lane masks and branches the same loop took 67 scalar
             // instructions per turn, which a lone wave waits for one by one;
-            // now it takes 39.  1080p terrain animation 144 -> 136 us, moving
+            // now it takes 34.  1080p terrain animation 144 -> 136 us, moving
             // camera 181 -> 167 us, 100 rays 44 -> 40 us.
             while (ev == EV_NONE) {
                 if (full == 0u) {
