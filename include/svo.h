@@ -116,9 +116,9 @@ typedef struct {
 
 /* Kernel configuration; svo_tune() picks one, svo_set_config() sets one.
    Zero fields select the library defaults.  A launch whose tables do not
-   fit the device's LDS per work-group under it lowers waves_per_block, by one
-   at a time, before it reports SVO_ERANGE; results never depend on the
-   configuration. */
+   fit the device's LDS under it takes the waves_per_block and blocks_per_cu
+   that keep most of its waves, before it reports SVO_ERANGE; results never
+   depend on the configuration. */
 typedef struct {
     uint32_t waves_per_block;   /* 1..16 wavefronts (64 lanes) per work-group */
     uint32_t blocks_per_cu;     /* work-groups per compute unit of the persistent grid (capped by what LDS and 32 waves per CU let reside) */

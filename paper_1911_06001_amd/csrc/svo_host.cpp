@@ -1044,16 +1044,6 @@ int queue_slot(svo_ctx* ctx, hipStream_t st, uint32_t& qslot) {
     return SVO_OK;
 }
 
-// Work-groups of the persistent grid per CU: the configured count, capped by
-// what can be resident at once (LDS per CU, 32 waves per CU), so that no
-// work-group waits for another to exit before it starts.
-uint32_t resident_blocks(const svo_ctx* ctx, const svo_config& c, size_t lds) {
-    uint32_t b = c.blocks_per_cu;
-    if (lds) b = std::min<uint32_t>(b, (uint32_t)(ctx->lds_per_cu / lds));
-    b = std::min<uint32_t>(b, 32u / c.waves_per_block);
-    return std::max<uint32_t>(b, 1u);
-}
-
 // A stride coprime with `tiles` near tiles / golden ratio: consecutive claims
 // land far apart in the image.
 uint64_t tile_stride(uint64_t tiles) {
@@ -1063,16 +1053,36 @@ uint64_t tile_stride(uint64_t tiles) {
     return s ? s : 1;
 }
 
-// Fit a launch into the per-work-group LDS limit: take waves out of the
-// work-group, one at a time (1,000 candidates leave room for 7 of 8 waves:
-// 1280x720 primary rays 452 us with 7, 497 with 6, 653 with 4, the next
-// number that loads the four SIMDs evenly).  Results never depend on them; a
-// configuration tuned on one scene may meet a batch whose tables are larger.
-// Returns the LDS bytes, above the limit if nothing fits.
-size_t fit_lds(const svo_ctx* ctx, const svo::TraceArgs& a, uint32_t& waves) {
-    size_t lds = svo::trace_lds_bytes(a, waves);
-    while (lds > ctx->max_lds && waves > 1) lds = svo::trace_lds_bytes(a, --waves);
-    return lds;
+// Fit a launch's shape into the LDS (and 32 waves per CU), so that no
+// work-group waits for another to exit before it starts: the configured waves
+// per work-group and work-groups per CU where they fit, else the shape that
+// keeps most of their waves.  Each work-group holds the launch's tables, so
+// that is often fewer and larger ones: tuned to 4 waves by 6 on one scene, a
+// batch of 10 jobs has room for 5 such work-groups (394 us) but for 3 of 8
+// waves (367 us).  Several work-groups load the four SIMDs evenly only with
+// multiples of 4 waves (4 of 6 waves: 415 us); one takes what fits (1,000
+// candidates leave room for 7 waves: 1280x720 primary rays 452 us; 497 with
+// 6, 653 with 4).  Results never depend on it.  Returns the LDS bytes of a
+// work-group, above the limit if nothing fits.
+size_t fit_lds(const svo_ctx* ctx, const svo::TraceArgs& a, svo_config& c) {
+    const uint32_t most = std::max(1u, std::min(c.blocks_per_cu, 32u / c.waves_per_block));
+    const uint32_t total = c.waves_per_block * most;
+    uint32_t waves = 0, blocks = 0;
+    for (uint32_t b = most; b >= 1; --b)
+        for (uint32_t w = std::min(16u, total / b); w >= 1; --w) {
+            if (w % 4 && w != c.waves_per_block && b > 1) continue;
+            if (svo::trace_lds_bytes(a, w) > std::min(ctx->max_lds, ctx->lds_per_cu / b)) continue;
+            if (w * b > waves * blocks) {
+                waves = w;
+                blocks = b;
+            }
+            break;
+        }
+    if (waves) {
+        c.waves_per_block = waves;
+        c.blocks_per_cu = blocks;
+    }
+    return svo::trace_lds_bytes(a, std::max(waves, 1u));
 }
 
 // Size LDS (see fit_lds) and launch.
@@ -1081,13 +1091,13 @@ int launch(svo_ctx* ctx, const svo_config& cfg, svo::TraceArgs& a, hipStream_t s
     a.tile_stride = tile_stride((a.n_rays + 63) / 64);
     a.tile_inv = 1.0 / (double)((a.n_rays + 63) / 64);
     svo_config c = cfg;
-    const size_t lds = fit_lds(ctx, a, c.waves_per_block);
+    const size_t lds = fit_lds(ctx, a, c);
     if (lds > ctx->max_lds) return fail(SVO_ERANGE, "launch needs %zu bytes of LDS per work-group", lds);
     svo::LaunchCfg L{};
     L.waves_per_block = c.waves_per_block;
     const uint64_t tiles = (a.n_rays + 63) / 64;
     const uint64_t want = (tiles + c.waves_per_block - 1) / c.waves_per_block;
-    const uint64_t cap = (uint64_t)ctx->n_cu * resident_blocks(ctx, c, lds);
+    const uint64_t cap = (uint64_t)ctx->n_cu * c.blocks_per_cu;
     L.blocks = (uint32_t)std::max<uint64_t>(1, std::min(want, cap));
     a.max_blocks = (uint32_t)cap;
     L.lds_bytes = lds;
@@ -1513,7 +1523,7 @@ int trace_batch(svo_ctx* ctx, const svo_job* jobs, uint32_t n_jobs, void* stream
             a.has_cam0 = 1;
             a.cam0 = P.jobs[0].cam;
         }
-        const size_t lds = fit_lds(ctx, a, cfg.waves_per_block);
+        const size_t lds = fit_lds(ctx, a, cfg);
         if (lds > ctx->max_lds) return fail(SVO_ERANGE, "batch needs %zu bytes of LDS per work-group", lds);
 
         if (P.jobs.size() == 1 && P.jobs[0].S->inline_tab && a.sort_cand) {
@@ -1674,10 +1684,10 @@ int svo_plan_create(svo_ctx* ctx, const svo_scene* scenes, uint32_t n_scenes, co
         a.stack_levels = pl->stack_cap;
         a.nest_levels = pl->nest_cap;
         fill_common(pl->cfg, a);
-        const size_t lds = fit_lds(ctx, a, pl->cfg.waves_per_block);
+        const size_t lds = fit_lds(ctx, a, pl->cfg);
         if (lds > ctx->max_lds) return fail(SVO_ERANGE, "plan needs %zu bytes of LDS per work-group", lds);
         pl->launch_cfg.waves_per_block = pl->cfg.waves_per_block;
-        pl->launch_cfg.blocks = (uint32_t)std::max<uint64_t>(1, (uint64_t)ctx->n_cu * resident_blocks(ctx, pl->cfg, lds));
+        pl->launch_cfg.blocks = (uint32_t)std::max<uint64_t>(1, (uint64_t)ctx->n_cu * pl->cfg.blocks_per_cu);
         pl->launch_cfg.lds_bytes = lds;
         a.max_blocks = pl->launch_cfg.blocks;
 

@@ -1,5 +1,5 @@
-// Which candidate path the library's host code picks for a launch, on the CPU
-// (test infrastructure: tests/test_host_routes.py compiles and runs it).  The
+// Which candidate path and shape the library's host code picks for a launch,
+// on the CPU (test infrastructure: tests/test_host_routes.py compiles and runs it).  The
 // host source is included whole and the HIP runtime and the kernels' launch
 // functions are stubs, so a launch ends in a look at its arguments.
 #include "../../paper_1911_06001_amd/csrc/svo_host.cpp"
@@ -8,6 +8,7 @@
 
 namespace {
 svo::TraceArgs launched;
+svo::LaunchCfg shape;
 }
 
 namespace svo {
@@ -16,10 +17,13 @@ hipError_t launch_ao_rays(const AoArgs&, hipStream_t) { return hipSuccess; }
 hipError_t launch_shade(const ShadeArgs&, hipStream_t) { return hipSuccess; }
 hipError_t static_scratch(int, unsigned char**) { return hipErrorNoDevice; }
 hipError_t launch_zero_words(uint32_t*, uint32_t, hipStream_t) { return hipSuccess; }
-size_t trace_lds_bytes(const TraceArgs& a, uint32_t) { return (size_t)a.n_frames * 64 + (size_t)a.n_bvh_total * sizeof(BvhNode); }
+size_t trace_lds_bytes(const TraceArgs& a, uint32_t waves) {   // tables and per-wave state, to the kilobyte
+    return (size_t)a.n_frames * 64 + (size_t)a.n_bvh_total * sizeof(BvhNode) + (size_t)waves * 5632;
+}
 hipError_t prepare_trace(size_t) { return hipSuccess; }
-hipError_t launch_trace(const TraceArgs& a, const LaunchCfg&, hipStream_t, const unsigned char*, size_t) {
+hipError_t launch_trace(const TraceArgs& a, const LaunchCfg& c, hipStream_t, const unsigned char*, size_t) {
     launched = a;
+    shape = c;
     return hipSuccess;
 }
 }  // namespace svo
@@ -80,11 +84,12 @@ svo_scene upload(svo_ctx& ctx, uint32_t n) {
 
 }  // namespace
 
-// routes_host CONTEXT TUNED CANDIDATES JOBS: sorted_candidates of the context
-// and of the scene's tuning (-1: not tuned); prints the path and hierarchy
-// nodes of a batch and of a plan, or what refused them.
+// routes_host CONTEXT TUNED CANDIDATES JOBS [WAVES BLOCKS]: sorted_candidates of
+// the context and of the scene's tuning (-1: not tuned), and the configured
+// shape; prints the path, the hierarchy nodes and the shape of a batch and of
+// a plan, or what refused them.
 int main(int argc, char** argv) {
-    if (argc != 5) return 2;
+    if (argc != 5 && argc != 7) return 2;
     const int tuned = std::atoi(argv[2]);
     const uint32_t n = (uint32_t)std::atoi(argv[3]), jobs = (uint32_t)std::atoi(argv[4]);
     svo_ctx ctx;
@@ -92,6 +97,10 @@ int main(int argc, char** argv) {
     ctx.max_lds = ctx.lds_per_cu = 163840;
     ctx.cfg = default_config();
     ctx.cfg.sorted_candidates = (uint32_t)std::atoi(argv[1]);
+    if (argc == 7) {
+        ctx.cfg.waves_per_block = (uint32_t)std::atoi(argv[5]);
+        ctx.cfg.blocks_per_cu = (uint32_t)std::atoi(argv[6]);
+    }
     std::vector<uint32_t> queue(svo::kQueueWords * kMaxStreams);
     ctx.d_queue = queue.data();
     const svo_scene h = upload(ctx, n);
@@ -117,7 +126,8 @@ int main(int argc, char** argv) {
     if (svo_trace_batch(&ctx, J.data(), jobs, nullptr))
         std::printf("batch refused: %s\n", svo_last_error());
     else
-        std::printf("batch %s %u\n", launched.sort_cand ? "one-by-one" : "hierarchy", launched.n_bvh_total);
+        std::printf("batch %s %u %ux%u\n", launched.sort_cand ? "one-by-one" : "hierarchy", launched.n_bvh_total,
+                    shape.waves_per_block, launched.max_blocks / (uint32_t)ctx.n_cu);
     svo_plan_limits lim{};
     lim.max_jobs = jobs;
     lim.max_frames = jobs * (1 + n);
@@ -125,7 +135,8 @@ int main(int argc, char** argv) {
     if (svo_plan_create(&ctx, &h, 1, &lim, &p) || svo_plan_set_jobs(&ctx, p, J.data(), jobs) || svo_plan_launch(&ctx, p, nullptr))
         std::printf("plan refused: %s\n", svo_last_error());
     else
-        std::printf("plan %s %u\n", launched.sort_cand ? "one-by-one" : "hierarchy", launched.n_bvh_total);
+        std::printf("plan %s %u %ux%u\n", launched.sort_cand ? "one-by-one" : "hierarchy", launched.n_bvh_total,
+                    shape.waves_per_block, launched.max_blocks / (uint32_t)ctx.n_cu);
     svo_plan_destroy(&ctx, p);
     svo_free_scene(&ctx, h);
     for (auto& b : ctx.batch) {
