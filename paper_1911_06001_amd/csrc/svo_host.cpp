@@ -724,8 +724,10 @@ int upload_frames(Scene& S, hipStream_t stream, bool to_device) {
 }
 
 // Copy a pool to the device in the device format (svo_internal.h), encoded
-// chunk by chunk on the way.
-hipError_t copy_pool(uint64_t* dev, const uint64_t* nodes, uint64_t n) {
+// chunk by chunk on the way.  rooted: it has been checked and is walked; a
+// pool without a root is neither, and svo_shade may read any word 1 of it, so
+// its nodes go as leaves.
+hipError_t copy_pool(uint64_t* dev, const uint64_t* nodes, uint64_t n, bool rooted) {
     constexpr uint64_t kChunk = 1u << 20;
     const bool packed = n <= svo::kPackedNodes;
     std::vector<uint64_t> buf(std::min(n, kChunk));
@@ -733,9 +735,9 @@ hipError_t copy_pool(uint64_t* dev, const uint64_t* nodes, uint64_t n) {
         const uint64_t cnt = std::min(kChunk, n - at);
         for (uint64_t k = 0; k < cnt; ++k) {
             const uint64_t w = nodes[at + k];
-            const uint32_t mask = nd_mask(w);
+            const uint32_t mask = rooted ? nd_mask(w) : 0u;
             uint32_t w0 = 0u, w1 = nd_w1(w);   // a leaf: 0 and its colour
-            if (nd_xform(w)) {
+            if (mask && nd_xform(w)) {
                 w0 = svo::kNodeXform | mask;
                 w1 &= ~kXform;
             } else if (mask) {
@@ -911,7 +913,7 @@ int svo_upload(svo_ctx* ctx, const uint64_t* nodes, uint64_t n_nodes, uint32_t r
                 return fail(SVO_ENOMEM, "allocation of frame tables failed");
             }
         }
-        const hipError_t e = copy_pool(S->d_nodes, nodes, n_nodes);
+        const hipError_t e = copy_pool(S->d_nodes, nodes, n_nodes, root != SVO_NONE);
         if (e != hipSuccess) {
             free_scene(*S);
             return fail(SVO_EDEVICE, "pool copy failed: %s", hipGetErrorString(e));

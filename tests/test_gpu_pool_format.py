@@ -143,3 +143,15 @@ def test_pool_sizes_with_a_device_table(ctx, oracle_lib, n_nodes, kind, path):
     parity.assert_parity(stats)
     assert stats["hits"] > 300
     ctx.free_scene(h)
+
+
+def test_pool_without_a_root_shades_as_uploaded(ctx):
+    """A pool without a root is not checked; any of its words may be shaded."""
+    import torch
+    nodes = np.random.default_rng(3).integers(0, 1 << 63, 4096, dtype=np.uint64) * np.uint64(2) + np.uint64(1)
+    h = ctx.upload(nodes, 0xFFFFFFFF, (0, 0, 0), 1.0, 20, np.zeros(0, np.uint32), np.zeros((0, 4), np.float32))
+    ids = torch.arange(4096, dtype=torch.int32, device="cuda")
+    img = ctx.shade(h, ids, 64, 64, tiled=False).cpu().numpy().view(np.uint32).ravel()
+    want = (nodes >> np.uint64(32)).astype(np.uint32)
+    assert np.array_equal(img & 0xFFFFFF, want & 0xFFFFFF)
+    ctx.free_scene(h)
